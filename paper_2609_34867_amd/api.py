@@ -441,9 +441,13 @@ def calib_block_grad(x: torch.Tensor, target: torch.Tensor, w_qkv: torch.Tensor,
 # --------------------------------------------------------------------------- W4A4 linear
 def w4a4_linear_workspace(M: int, N_out: int, K_in: int, device) -> Optional[torch.Tensor]:
     n = lib().p4q_w4a4_linear_workspace_bytes(M, N_out, K_in)
-    # zero-filled: its head holds arrival counters that must start at zero
-    # (every call leaves them zero again)
-    return None if n == 0 else torch.zeros(n, dtype=torch.uint8, device=device)
+    if n == 0:
+        return None
+    # its head holds arrival counters that must start at zero (every call
+    # leaves them zero again)
+    ws = torch.empty(n, dtype=torch.uint8, device=device)
+    ws[:4096].zero_()
+    return ws
 
 
 def w4a4_linear(a_codes: torch.Tensor, a_scales: torch.Tensor, w_codes: torch.Tensor,
@@ -453,8 +457,9 @@ def w4a4_linear(a_codes: torch.Tensor, a_scales: torch.Tensor, w_codes: torch.Te
     """W4A4 linear (p4q_w4a4_linear): a_codes [M, K_in/2], w_codes [N_out, K_in/2]
     -> y [M, N_out] (out_dtype); also the int32 accumulators when return_acc.
     Without `workspace` one of the size the library asks for is allocated
-    (small M splits K across work-groups with it); a smaller one, e.g.
-    empty, runs the unsplit kernel.  Results are identical either way."""
+    (small M splits K across work-groups with it, large products take the
+    6-bit matrix path); a smaller one, e.g. empty, runs without it.  Results
+    are identical either way."""
     if a_codes.dim() != 2 or w_codes.dim() != 2:
         raise ValueError("a_codes and w_codes must be 2-D [rows, K_in/2]")
     M, kb = a_codes.shape

@@ -142,6 +142,13 @@ hipError_t launch_w4a4_gemm(int M, int N, int K, const uint8_t *a, const float *
                             int64_t ldy, int32_t *acc_out, void *ws, size_t ws_bytes,
                             hipStream_t stream);
 
+// The same on the 6-bit matrix instructions (w4a4_f6.hip): ws holds
+// gemm_f6_bytes(M, N, K) bytes, 16-byte aligned.
+size_t gemm_f6_bytes(int M, int N, int K);
+hipError_t launch_w4a4_gemm_f6(int M, int N, int K, const uint8_t *a, const float *sa,
+                               const uint8_t *w, const float *sw, p4q_dtype out_dt, void *y,
+                               int64_t ldy, int32_t *acc_out, void *ws, hipStream_t stream);
+
 // ---- diagnostics (diag.hip) ----------------------------------------------------
 hipError_t launch_diag_mfma_i8(int blocks, int iters, int32_t *out, hipStream_t stream);
 hipError_t launch_diag_read(const void *src, size_t bytes, int blocks, uint32_t *out,

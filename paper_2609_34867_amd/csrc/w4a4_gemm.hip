@@ -13,6 +13,7 @@
 // permutation of k on both sides and accumulates 256 * acc exactly
 // (|256 * acc| <= 256 * 64 * K_in < 2^31 for K_in <= 131072); an arithmetic
 // shift by 8 recovers acc.
+#include "gemm_device.h"
 #include "p4q_internal.h"
 
 #include <algorithm>
@@ -20,7 +21,6 @@
 namespace p4q {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 
@@ -403,62 +403,6 @@ constexpr int kMidStages = 3;
 template <int BMT> constexpr int l_stages() { return BMT == 256 ? 3 : kMidStages; }
 template <int BMT> constexpr int l_stage() { return (BMT + L_BN) * BKB; }   // packed codes
 template <int BMT> constexpr int l_scale_off() { return l_stages<BMT>() * l_stage<BMT>(); }
-constexpr int kXcds = 8;
-constexpr int kGroupM = 8;
-
-typedef __attribute__((address_space(3))) void *lds_ptr_t;
-
-// Buffer descriptor of a raw byte range (stride 0, range-checked: loads past
-// `bytes` return zeros).
-__device__ __forceinline__ v4i buffer_desc(const void *base, uint32_t bytes) {
-    const uint64_t b = reinterpret_cast<uint64_t>(base);
-    return v4i{(int)(uint32_t)b, (int)((b >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
-}
-
-// 16 (or 4) bytes per lane from a buffer straight into LDS at lds + 16 *
-// lane (4 * lane).  Issued as inline asm so the compiler does not add its
-// conservative vmcnt(0) before every LDS read (it cannot tell the ring slots
-// apart); the kernel waits with explicit vmcnt counts instead.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(v4i desc, uint32_t voffset, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-                 :
-                 : "v"(voffset), "s"(desc), "s"(lds_addr)
-                 : "memory", "m0");
-}
-__device__ __forceinline__ void dma4(v4i desc, uint32_t voffset, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\tbuffer_load_dword %0, %1, 0 offen lds"
-                 :
-                 : "v"(voffset), "s"(desc), "s"(lds_addr)
-                 : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-__device__ __forceinline__ uint32_t lds_addr(const void *p) {
-    return (uint32_t)(size_t)(lds_ptr_t)p;
-}
-
-// Work-group id -> logical index such that the ids of one XCD (dealt
-// round-robin) form a contiguous range of [0, total).
-__device__ __forceinline__ int xcd_logical(int wg, int total) {
-    const int q = total / kXcds, r = total % kXcds;
-    const int x = wg % kXcds, i = wg / kXcds;
-    return (x < r) ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
-}
-
-// logical index -> tile, walking groups of kGroupM tile rows column by column
-__device__ __forceinline__ void grouped_tile(int logical, int tiles_m, int tiles_n, int &tm,
-                                             int &tn) {
-    const int per_group = kGroupM * tiles_n;
-    const int g = logical / per_group;
-    const int first_m = g * kGroupM;
-    const int gsize = min(tiles_m - first_m, kGroupM);
-    const int in_g = logical - g * per_group;
-    tm = first_m + in_g % gsize;
-    tn = in_g / gsize;
-}
-
 // Gram mode (M == N, A == W): only tiles holding an entry on or above the
 // diagonal, i.e. tn >= 2 tm for 256 x 128 tiles; row tm of tiles holds
 // tiles_n - 2 tm of them.  Same XCD-contiguous dealing as xcd_logical.
@@ -1328,6 +1272,24 @@ __global__ __launch_bounds__(64 * NW) void k_w4a4_gemv(const uint8_t *__restrict
 static bool use_large_tiles(int M, int N) { return M >= 1024 && N >= 1024; }
 static bool use_mid_tiles(int M, int N) { return M > 16 && M < 1024 && N >= 1024; }
 
+// The 6-bit matrix path (w4a4_f6.hip; needs the caller's workspace) against
+// the int8 tiles.  It pays a pass that rewrites both operands (9 us at 4096 +
+// 4096 rows of K = 4096, 22 us at 11264 + 12288) and its 256 x 256 tiles take
+// one CU each, so it needs rows to spread the pass over and tiles for more
+// than half of the CUs.  Measured, int8 / 6-bit us: K = 4096, M x N =
+// 11264 x 22016: 736 / 532, 4096 x 12288: 146 / 121, 1536 x 12288: 80 / 78,
+// 4096 x 4096 (256 tiles): 50 / 47; 1024 x 22016: 82 / 86, 3072 x 4096 (192
+// tiles): 43 / 45, 2048 x 4096 (128 tiles): 35 / 42.  Longer rows hide more
+// of the per-tile cost: K = 11008, 2304 x 4096 (144 tiles): 98 / 82, but
+// 2048 x 4096 (128 tiles) 83 / 82.  The operands' copy is kept under 1 GiB.
+constexpr int kF6MinRows = 1536;
+static bool use_f6(int M, int N, int K) {
+    if (!use_large_tiles(M, N) || M < kF6MinRows) return false;
+    const int64_t T = (((int64_t)M + 255) / 256) * (((int64_t)N + 255) / 256);
+    return (T >= 224 || (T > 128 && K >= 5120)) && T < (1 << 30) &&
+           gemm_f6_bytes(M, N, K) <= ((size_t)1 << 30);
+}
+
 // Tile height of the mid path: 128 rows, or 64 where 128-row tiles would
 // leave most CUs with a single block (fewer than 1.5 tiles per CU) and
 // K_in <= 4096.  64-row tiles are less efficient per tile (their fragment
@@ -1425,6 +1387,7 @@ hipError_t gemm_workspace_clear(void *ws, size_t ws_bytes, hipStream_t stream) {
 }
 
 size_t gemm_workspace_bytes(int M, int N, int K) {
+    if (use_f6(M, N, K)) return kArrivalBytes + gemm_f6_bytes(M, N, K);
     if (use_mid_tiles(M, N)) return mid_split_bytes(mid_plan(M, N, K));
     const int S = small_m_splits(M, N, K);
     return S > 1 ? (size_t)S * M * N * 4 : 0;
@@ -1462,6 +1425,9 @@ hipError_t launch_w4a4_gemm(int M, int N, int K, const uint8_t *a, const float *
     const unsigned eb = (unsigned)(((int64_t)M * N / 4 + 255) / 256);   // split-K epilogue blocks
     if (use_large_tiles(M, N) || use_mid_tiles(M, N)) {
         const bool large = use_large_tiles(M, N);
+        if (large && use_f6(M, N, K) && ws_ok)
+            return launch_w4a4_gemm_f6(M, N, K, a, sa, w, sw, out_dt, y, ldy, acc_out,
+                                       static_cast<uint8_t *>(ws) + kArrivalBytes, stream);
         const MidPlan plan = large ? MidPlan{} : mid_plan(M, N, K);
         const int bm = large ? L_BM : plan.bm;
         const int tiles_m = (M + bm - 1) / bm, tiles_n = (N + L_BN - 1) / L_BN;

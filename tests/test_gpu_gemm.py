@@ -369,3 +369,53 @@ def test_split_k_graph_replays(shape):
         torch.cuda.synchronize()
         assert (m := first_mismatch(bits(to_np(y2)), bits(ry))) is None, (rep, m)
     del g
+
+
+@pytest.mark.parametrize("shape,ldy,off", [((1537, 4700, 5152), 4700, 0), ((1800, 7000, 160), 7003, 0),
+                                           ((1536, 9500, 128), 9500, 1), ((2048, 7168, 256), 7168, 0)])
+def test_f6_path(shape, ldy, off):
+    """The 6-bit matrix path: tiles ragged in M and N, an odd number of
+    128-value stages and a ragged last one (5152), fewer stages than the ring
+    (128, 160, 256), rows and a base that allow no 16-byte stores.  Exact sums:
+    equal to the oracle bit for bit, in both output types."""
+    M, N, K = shape
+    dev = torch.device("cuda:0")
+    ws = p4q.w4a4_linear_workspace(M, N, K, dev)
+    assert ws is not None and ws.numel() > 3 * K * (M + N) // 4
+    ws[4096:].fill_(0xFF)                      # stale bytes behind the counters reach no output
+    ap, sa, wp, sw = codes_for(M, N, K, seed=M + N + K)
+    a, s_a, w, s_w = to_gpu(ap), to_gpu(sa), to_gpu(wp), to_gpu(sw)
+    for dt, name in ((torch.bfloat16, "bf16"), (torch.float16, "fp16")):
+        racc, ry = oracle.w4a4_linear(ap, sa, wp, sw, name)
+        for with_acc in (True, False):
+            buf = torch.full((M * ldy + 64,), 7.0, dtype=dt, device=dev)
+            y = buf[2 * off:2 * off + M * ldy].view(M, ldy)[:, :N]
+            acc = torch.zeros((M, N), dtype=torch.int32, device=dev) if with_acc else None
+            p4q.w4a4_linear(a, s_a, w, s_w, y=y, acc_out=acc, workspace=ws)
+            torch.cuda.synchronize()
+            if with_acc:
+                assert (m := first_mismatch(to_np(acc), racc.astype(np.int32))) is None, (name, m)
+            assert (m := first_mismatch(bits(to_np(y.contiguous())), bits(ry))) is None, (name, with_acc, m)
+            assert bool((buf[:2 * off] == 7).all()) and bool((buf[2 * off + M * ldy:] == 7).all())
+    assert int(ws[:4096].count_nonzero()) == 0
+
+
+def test_f6_path_largest_sums():
+    """|acc| = 64 K = 2^23 at the largest K_in (all codes -8), and random
+    codes there against the int8 path: fp32 accumulation stays exact."""
+    M, N, K = 1536, 6144, 131072
+    dev = torch.device("cuda:0")
+    one_a, one_w = torch.ones(M, device=dev), torch.ones(N, device=dev)
+    ws = p4q.w4a4_linear_workspace(M, N, K, dev)
+    assert ws.numel() > 4096 + 3 * K * (M + N) // 4 - 1
+    a = torch.full((M, K // 2), 0x88, dtype=torch.uint8, device=dev)
+    w = torch.full((N, K // 2), 0x88, dtype=torch.uint8, device=dev)
+    _, acc = p4q.w4a4_linear(a, one_a, w, one_w, return_acc=True, workspace=ws)
+    assert bool((acc == 64 * K).all())
+    g = torch.Generator(device=dev).manual_seed(5)
+    a.random_(0, 256, generator=g)
+    w.random_(0, 256, generator=g)
+    none = torch.empty(0, dtype=torch.uint8, device=dev)
+    _, acc = p4q.w4a4_linear(a, one_a, w, one_w, return_acc=True, workspace=ws)
+    _, ref = p4q.w4a4_linear(a, one_a, w, one_w, return_acc=True, workspace=none)
+    assert torch.equal(acc, ref)
