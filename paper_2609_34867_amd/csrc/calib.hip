@@ -1039,108 +1039,177 @@ __global__ __launch_bounds__(kThreads) void k_blk_rope(T *__restrict__ z, int64_
     }
 }
 
-template <typename T> __device__ __forceinline__ float ldv(const T *p, int64_t i);
-template <> __device__ __forceinline__ float ldv<float>(const float *p, int64_t i) { return p[i]; }
-template <> __device__ __forceinline__ float ldv<uint16_t>(const uint16_t *p, int64_t i) {
-    return f16v(p[i]);
+// Four consecutive elements as fp32, the first n of them valid (the others
+// 0).  vec: one vector load, which may read past n within the padded row;
+// otherwise element by element.
+__device__ __forceinline__ float4 ld4(const float *p, bool vec, int n) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (n <= 0) return v;
+    if (vec) {
+        v = *reinterpret_cast<const float4 *>(p);
+        if (n < 4) v = make_float4(v.x, n > 1 ? v.y : 0.f, n > 2 ? v.z : 0.f, 0.f);
+        return v;
+    }
+    v.x = p[0];
+    if (n > 1) v.y = p[1];
+    if (n > 2) v.z = p[2];
+    if (n > 3) v.w = p[3];
+    return v;
+}
+__device__ __forceinline__ float4 ld4(const uint16_t *p, bool vec, int n) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (n <= 0) return v;
+    if (vec && n >= 4) {
+        const uint2 w = *reinterpret_cast<const uint2 *>(p);
+        return make_float4(lo_f32<false>(w.x), hi_f32<false>(w.x), lo_f32<false>(w.y), hi_f32<false>(w.y));
+    }
+    v.x = f16v(p[0]);
+    if (n > 1) v.y = f16v(p[1]);
+    if (n > 2) v.z = f16v(p[2]);
+    if (n > 3) v.w = f16v(p[3]);
+    return v;
 }
 
-// Batched strided GEMM with fp32 accumulation (the attention products of
-// one block): C[b](i, j) = alpha sum_k A[b](i, k) B[b](k, j); A element
-// (i, k) at A + b sAb + i sAi + k sAk, B (k, j) at B + b sBb + k sBk + j sBj,
-// C (i, j) at C + b sCb + i sCi + j.  64 x 64 tiles, 32 k per stage, 256
-// threads with 4 x 4 outputs each; the next stage's elements are loaded into
-// registers while the current stage is multiplied.  band: 0 all k; 1 only
-// k <= i (A is lower triangular: P or dS); 2 only k >= i (A is upper
-// triangular: P^T or dS^T); 3 full k, tiles strictly above the diagonal
-// (j > i everywhere) skipped (their entries are never read).
+// Batched strided GEMM in fp32 (the attention products of one block) on
+// v_mfma_f32_32x32x2_f32: C[b](i, j) = alpha sum_k A[b](i, k) B[b](k, j); A
+// element (i, k) at A + b sAb + i sAr + k sAk, B (k, j) at B + b sBb + k sBk +
+// j sBr, C (i, j) at C + b sCb + i sCi + j; AK / BK: the operand's unit stride
+// is along k (otherwise along its row i / column j).  64 x 64 tiles, 4
+// wavefronts of 32 x 32; 32 k per stage, two LDS buffers, the next stage's
+// elements on their way in registers meanwhile.  band: 0 all k; 1 only k <= i
+// (A is lower triangular: P or dS); 2 only k >= i (A is upper triangular: P^T
+// or dS^T); 3 full k, tiles strictly above the diagonal (j > i everywhere)
+// skipped (their entries are never read).  In band 1 the longest tiles come
+// first (in band 2 they do in natural order).
+//
+// Bound by load latency and the fp32 matrix rate (157 TFLOP/s).  At M = 384,
+// 32 heads of 128 the six products of a block take 136 us (18-28 us each),
+// against 320 us on the vector units, whose multiply-adds need two LDS reads
+// for every four.
+//
+// The instruction adds its two products one after the other, each with one
+// rounding, and lane half h carries k = 2 s + h of step s, so every sum runs
+// over k in ascending order: the same results, bit for bit, as a chain of
+// fused multiply-adds.
+//
+// LDS: an operand with unit stride along k as [row][k], rows of 36 floats (16
+// lanes' 16-byte reads fall in distinct banks), the even k of every eight
+// before the odd ones, so that one read holds a lane's four steps; one with
+// unit stride along the row as [k][row], rows of 72 floats.
 constexpr int GB = 64, GK = 32;
-template <typename TA, typename TB, bool C16>
+constexpr int kGLds = GB * 36;               // = GK * 72 floats
+static_assert(kGLds == GK * 72, "LDS operand");
+
+template <typename TA, typename TB, bool C16, bool AK, bool BK>
 __global__ __launch_bounds__(kThreads) void k_blk_bgemm(
-    const TA *__restrict__ A, int64_t sAb, int64_t sAi, int64_t sAk, const TB *__restrict__ B,
-    int64_t sBb, int64_t sBk, int64_t sBj, void *__restrict__ Cv, int64_t sCb, int64_t sCi, int I,
-    int J, int K, float alpha, int band) {
-    __shared__ float As[GK][GB + 1];
-    __shared__ float Bs[GK][GB + 1];
-    const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
-    const int i0 = blockIdx.y * GB, j0 = blockIdx.x * GB, b = blockIdx.z;
+    const TA *__restrict__ A, int64_t sAb, int64_t sAr, int64_t sAk, bool vecA,
+    const TB *__restrict__ B, int64_t sBb, int64_t sBr, int64_t sBk, bool vecB,
+    void *__restrict__ Cv, int64_t sCb, int64_t sCi, int I, int J, int K, float alpha, int band) {
+    __shared__ __attribute__((aligned(16))) float As[2][kGLds], Bs[2][kGLds];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int wi = wave >> 1, wj = wave & 1, r32 = lane & 31, h = lane >> 5;
+    const int by = (band == 1) ? (int)gridDim.y - 1 - (int)blockIdx.y : (int)blockIdx.y;
+    const int i0 = by * GB, j0 = blockIdx.x * GB, b = blockIdx.z;
     if (band == 3 && j0 > i0 + GB - 1) return;
     A += b * sAb;
     B += b * sBb;
     int kbeg = 0, kend = K;
     if (band == 1) kend = min(K, i0 + GB);
     if (band == 2) kbeg = i0;
-    float acc[4][4];
+
+    // this thread's two groups of four elements of a stage: (row, k)
+    auto place = [&](int q, bool kfast, int &r, int &k) __attribute__((always_inline)) {
+        r = kfast ? (t >> 3) + 32 * q : 4 * (t & 15);
+        k = kfast ? 4 * (t & 7) : (t >> 4) + 16 * q;
+    };
+    float4 ra[2], rb[2];
+    auto load = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = 0.0f;
-    const bool a_kfast = (sAk == 1), b_jfast = (sBj == 1);
-    // this thread's 8 elements of each stage: A (kk, ii), B (kb, jj)
-    int akk[8], aii[8], bkk[8], bjj[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int e = t + kThreads * q;
-        akk[q] = a_kfast ? (e & 31) : (e >> 6);
-        aii[q] = a_kfast ? (e >> 5) : (e & 63);
-        bkk[q] = b_jfast ? (e >> 6) : (e & 31);
-        bjj[q] = b_jfast ? (e & 63) : (e >> 5);
-    }
-    float ra[8], rb[8];
-    auto load = [&](int k0) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int i = i0 + aii[q], k = k0 + akk[q];
-            ra[q] = (i < I && k < kend) ? ldv<TA>(A, (int64_t)i * sAi + (int64_t)k * sAk) : 0.0f;
-            const int j = j0 + bjj[q], kq = k0 + bkk[q];
-            rb[q] = (j < J && kq < kend) ? ldv<TB>(B, (int64_t)kq * sBk + (int64_t)j * sBj) : 0.0f;
+        for (int q = 0; q < 2; ++q) {
+            int r, k;
+            place(q, AK, r, k);
+            {
+                const int i = i0 + r, kk = k0 + k;
+                const int n = AK ? (i < I ? kend - kk : 0) : (kk < kend ? I - i : 0);
+                ra[q] = ld4(A + (int64_t)i * sAr + (int64_t)kk * sAk, vecA, n);
+            }
+            place(q, BK, r, k);
+            {
+                const int j = j0 + r, kk = k0 + k;
+                const int n = BK ? (j < J ? kend - kk : 0) : (kk < kend ? J - j : 0);
+                rb[q] = ld4(B + (int64_t)j * sBr + (int64_t)kk * sBk, vecB, n);
+            }
         }
     };
-    if (kbeg < kend) load(kbeg);
-    for (int k0 = kbeg; k0 < kend; k0 += GK) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            As[akk[q]][aii[q]] = ra[q];
-            Bs[bkk[q]][bjj[q]] = rb[q];
+    auto put = [&](float *s, bool kfast, int r, int k, float4 v) __attribute__((always_inline)) {
+        if (kfast) {
+            float *d = s + r * 36 + (k & ~7) + ((k & 4) >> 1);
+            *reinterpret_cast<float2 *>(d) = make_float2(v.x, v.z);
+            *reinterpret_cast<float2 *>(d + 4) = make_float2(v.y, v.w);
+        } else {
+            *reinterpret_cast<float4 *>(s + k * 72 + r) = v;
         }
-        __syncthreads();
-        if (k0 + GK < kend) load(k0 + GK);          // in flight during this stage
-#pragma unroll 8
-        for (int kk = 0; kk < GK; ++kk) {
-            float a[4], bv[4];
+    };
+    auto store = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) a[r] = As[kk][ty + 16 * r];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) bv[c] = Bs[kk][tx + 16 * c];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[r][c] = __builtin_fmaf(a[r], bv[c], acc[r][c]);
+        for (int q = 0; q < 2; ++q) {
+            int r, k;
+            place(q, AK, r, k);
+            put(As[buf], AK, r, k, ra[q]);
+            place(q, BK, r, k);
+            put(Bs[buf], BK, r, k, rb[q]);
         }
+    };
+    auto frag = [&](const float *s, bool kfast, int r, int u) __attribute__((always_inline)) {
+        if (kfast) return *reinterpret_cast<const float4 *>(s + r * 36 + 8 * u + 4 * h);
+        const float *c = s + (8 * u + h) * 72 + r;
+        return make_float4(c[0], c[2 * 72], c[4 * 72], c[6 * 72]);
+    };
+
+    v16f acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+    if (kbeg < kend) {
+        load(kbeg);
+        store(0);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int k0 = kbeg; k0 < kend; k0 += GK, buf ^= 1) {
+        const bool more = k0 + GK < kend;
+        if (more) load(k0 + GK);
+#pragma unroll
+        for (int u = 0; u < GK / 8; ++u) {
+            const float4 a4 = frag(As[buf], AK, 32 * wi + r32, u), b4 = frag(Bs[buf], BK, 32 * wj + r32, u);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4.y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4.z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, b4.w, acc, 0, 0, 0);
+        }
+        if (more) store(buf ^ 1);
         __syncthreads();
     }
+    // lane holds column r32 and rows 8 (e / 4) + 4 h + e % 4
+    const int j = j0 + 32 * wj + r32;
+    if (j >= J) return;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = i0 + ty + 16 * r;
+    for (int e = 0; e < 16; ++e) {
+        const int i = i0 + 32 * wi + 8 * (e >> 2) + 4 * h + (e & 3);
         if (i >= I) continue;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int j = j0 + tx + 16 * c;
-            if (j >= J) continue;
-            const int64_t o = b * sCb + (int64_t)i * sCi + j;
-            if constexpr (C16) static_cast<uint16_t *>(Cv)[o] = to_f16(alpha * acc[r][c]);
-            else static_cast<float *>(Cv)[o] = alpha * acc[r][c];
-        }
+        const int64_t o = b * sCb + (int64_t)i * sCi + j;
+        if constexpr (C16) static_cast<uint16_t *>(Cv)[o] = to_f16(alpha * acc[e]);
+        else static_cast<float *>(Cv)[o] = alpha * acc[e];
     }
 }
 
-// Causal softmax of every row of S [H][M][M] (already scaled) in place: P
+// Causal softmax of every row of S [H][M][ld] (already scaled) in place: P
 // over j <= i, zeros beyond.  One wavefront per row.
-__global__ __launch_bounds__(kThreads) void k_blk_softmax(float *__restrict__ S, int M, int rows) {
+__global__ __launch_bounds__(kThreads) void k_blk_softmax(float *__restrict__ S, int M, int64_t ld,
+                                                         int rows) {
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (row >= rows) return;
     const int i = row % M;
-    float *p = S + (int64_t)row * M;
+    float *p = S + (int64_t)row * ld;
     float mx = -INFINITY;
     for (int j = lane; j <= i; j += 64) mx = fmaxf(mx, p[j]);
 #pragma unroll
@@ -1153,15 +1222,15 @@ __global__ __launch_bounds__(kThreads) void k_blk_softmax(float *__restrict__ S,
     for (int j = lane; j < M; j += 64) p[j] = (j <= i) ? expf(p[j] - mx) * inv : 0.0f;
 }
 
-// dS = P (dP - sum_l P dP) over j <= i, zeros beyond; dP [H][M][M] in place
+// dS = P (dP - sum_l P dP) over j <= i, zeros beyond; dP [H][M][ld] in place
 __global__ __launch_bounds__(kThreads) void k_blk_softmax_bwd(const float *__restrict__ P,
                                                              float *__restrict__ dP, int M,
-                                                             int rows) {
+                                                             int64_t ld, int rows) {
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (row >= rows) return;
     const int i = row % M;
-    const float *p = P + (int64_t)row * M;
-    float *g = dP + (int64_t)row * M;
+    const float *p = P + (int64_t)row * ld;
+    float *g = dP + (int64_t)row * ld;
     double s = 0.0;
     for (int j = lane; j <= i; j += 64) s += (double)p[j] * g[j];
 #pragma unroll
@@ -1339,6 +1408,10 @@ void block_groups(int d, int f, BlockGroup *g) {
     }
 }
 
+// row stride of the score matrices P and dP [H][M][ld]: whole groups of four
+// floats (what lies past column M is never used)
+inline int64_t score_ld(int M) { return ((int64_t)M + 3) / 4 * 4; }
+
 size_t block_carve(int M, int d, int f, int H, uint8_t *base, BlockWs *w) {
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -1356,7 +1429,7 @@ size_t block_carve(int M, int d, int f, int H, uint8_t *base, BlockWs *w) {
         calib_carve(g.p, M, g.N, g.K, cbase, &g.c);
         g.gpart = g.dx ? reinterpret_cast<float *>(take((size_t)g.p.nsA * M * g.K * 4)) : nullptr;
     }
-    const size_t Md = (size_t)M * d, Mf = (size_t)M * f, HMM = (size_t)H * M * M;
+    const size_t Md = (size_t)M * d, Mf = (size_t)M * f, HMM = (size_t)H * M * score_ld(M);
     auto h16 = [&](size_t n) { return reinterpret_cast<uint16_t *>(take(n * 2)); };
     auto f32 = [&](size_t n) { return reinterpret_cast<float *>(take(n * 4)); };
     b.n1 = h16(Md); b.qkv = h16(3 * Md); b.O = h16(Md); b.o_out = h16(Md); b.h = h16(Md);
@@ -1439,14 +1512,23 @@ hipError_t group_backward(BlockGroup &g, int M, const float *G, int64_t ldg, con
     return hipGetLastError();
 }
 
-// C[b] = alpha A[b] B[b] over a grid of 64 x 64 tiles (see k_blk_bgemm)
-template <typename TA, typename TB, bool C16>
-void bgemm(const TA *A, int64_t sAb, int64_t sAi, int64_t sAk, const TB *B, int64_t sBb,
-           int64_t sBk, int64_t sBj, void *C, int64_t sCb, int64_t sCi, int I, int J, int K,
-           int batch, float alpha, int band, hipStream_t stream) {
-    hipLaunchKernelGGL((k_blk_bgemm<TA, TB, C16>), dim3((J + GB - 1) / GB, (I + GB - 1) / GB, batch),
-                       dim3(kThreads), 0, stream, A, sAb, sAi, sAk, B, sBb, sBk, sBj, C, sCb, sCi,
-                       I, J, K, alpha, band);
+// C[b] = alpha A[b] B[b] over a grid of 64 x 64 tiles (see k_blk_bgemm).  An
+// operand is loaded four elements at a time when its rows, its batches and
+// its base allow it (head dimensions that are multiples of 4; the score
+// matrices' rows are padded for it).
+template <typename TA, typename TB, bool C16, bool AK, bool BK>
+void bgemm(const TA *A, int64_t sAb, int64_t lda, const TB *B, int64_t sBb, int64_t ldb, void *C,
+           int64_t sCb, int64_t sCi, int I, int J, int K, int batch, float alpha, int band,
+           hipStream_t stream) {
+    auto vec = [](const void *p, size_t esize, int64_t sb, int64_t ld) {
+        return sb % 4 == 0 && ld % 4 == 0 && reinterpret_cast<uintptr_t>(p) % (4 * esize) == 0;
+    };
+    const bool va = vec(A, sizeof(TA), sAb, lda), vb = vec(B, sizeof(TB), sBb, ldb);
+    hipLaunchKernelGGL((k_blk_bgemm<TA, TB, C16, AK, BK>),
+                       dim3((J + GB - 1) / GB, (I + GB - 1) / GB, batch), dim3(kThreads), 0, stream, A,
+                       sAb, AK ? lda : (int64_t)1, AK ? (int64_t)1 : lda, va, B, sBb,
+                       BK ? ldb : (int64_t)1, BK ? (int64_t)1 : ldb, vb, C, sCb, sCi, I, J, K, alpha,
+                       band);
 }
 
 hipError_t calib_block_run(int M, int d, int f, int H, const uint16_t *x, const float *target,
@@ -1468,6 +1550,7 @@ hipError_t calib_block_run(int M, int d, int f, int H, const uint16_t *x, const 
     const int64_t Md = (int64_t)M * d, Mf = (int64_t)M * f;
     const unsigned ebl = (unsigned)((Md + kThreads - 1) / kThreads);
     const int rows = H * M;
+    const int64_t ldP = score_ld(M), sP = (int64_t)M * ldP;
 
     // ---- forward
     // the forward GEMMs' split-K arrival counters live in this call's workspace
@@ -1484,11 +1567,12 @@ hipError_t calib_block_run(int M, int d, int f, int H, const uint16_t *x, const 
     hipLaunchKernelGGL((k_blk_rope<false, uint16_t>), dim3((unsigned)((nrope + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, stream, b.qkv, ld3, M, H, D, (const float2 *)b.rope);
     // S = q k^T / sqrt(D) (causal tiles only), P = softmax, O = P v
-    bgemm<uint16_t, uint16_t, false>(b.qkv, D, ld3, 1, b.qkv + d, D, 1, ld3, b.P, (int64_t)M * M, M,
-                                     M, M, D, H, isd, 3, stream);
-    hipLaunchKernelGGL(k_blk_softmax, dim3((rows + 3) / 4), dim3(kThreads), 0, stream, b.P, M, rows);
-    bgemm<float, uint16_t, true>(b.P, (int64_t)M * M, M, 1, b.qkv + 2 * d, D, ld3, 1, b.O, D, d, M,
-                                 D, M, H, 1.0f, 1, stream);
+    bgemm<uint16_t, uint16_t, false, true, true>(b.qkv, D, ld3, b.qkv + d, D, ld3, b.P, sP, ldP, M, M,
+                                                 D, H, isd, 3, stream);
+    hipLaunchKernelGGL(k_blk_softmax, dim3((rows + 3) / 4), dim3(kThreads), 0, stream, b.P, M, ldP,
+                       rows);
+    bgemm<float, uint16_t, true, true, false>(b.P, sP, ldP, b.qkv + 2 * d, D, ld3, b.O, D, d, M, D, M,
+                                              H, 1.0f, 1, stream);
     if ((e = group_forward(b.g[kGO], M, b.O, w[kGO], sg[kGO], clip_a[kGO], clip_w + cwo[kGO],
                            b.o_out, d, b.gemm_ws, b.gemm_ws_bytes, stream)) != hipSuccess)
         return e;
@@ -1529,16 +1613,16 @@ hipError_t calib_block_run(int M, int d, int f, int H, const uint16_t *x, const 
         return e;
     // dP = dO v^T (causal tiles), dS = P (dP - rowsum(P dP)); dq = dS k / sqrt(D),
     // dk = dS^T q / sqrt(D), dv = P^T dO, into the fused d(q|k|v) rows
-    bgemm<float, uint16_t, false>(b.dO, D, d, 1, b.qkv + 2 * d, D, 1, ld3, b.dP, (int64_t)M * M, M,
-                                  M, M, D, H, 1.0f, 3, stream);
+    bgemm<float, uint16_t, false, true, true>(b.dO, D, d, b.qkv + 2 * d, D, ld3, b.dP, sP, ldP, M, M,
+                                              D, H, 1.0f, 3, stream);
     hipLaunchKernelGGL(k_blk_softmax_bwd, dim3((rows + 3) / 4), dim3(kThreads), 0, stream, b.P,
-                       b.dP, M, rows);
-    bgemm<float, uint16_t, false>(b.dP, (int64_t)M * M, M, 1, b.qkv + d, D, ld3, 1, b.dqkv, D, ld3,
-                                  M, D, M, H, isd, 1, stream);
-    bgemm<float, uint16_t, false>(b.dP, (int64_t)M * M, 1, M, b.qkv, D, ld3, 1, b.dqkv + d, D, ld3,
-                                  M, D, M, H, isd, 2, stream);
-    bgemm<float, float, false>(b.P, (int64_t)M * M, 1, M, b.dO, D, d, 1, b.dqkv + 2 * d, D, ld3, M,
-                               D, M, H, 1.0f, 2, stream);
+                       b.dP, M, ldP, rows);
+    bgemm<float, uint16_t, false, true, false>(b.dP, sP, ldP, b.qkv + d, D, ld3, b.dqkv, D, ld3, M, D,
+                                               M, H, isd, 1, stream);
+    bgemm<float, uint16_t, false, false, false>(b.dP, sP, ldP, b.qkv, D, ld3, b.dqkv + d, D, ld3, M, D,
+                                                M, H, isd, 2, stream);
+    bgemm<float, float, false, false, false>(b.P, sP, ldP, b.dO, D, d, b.dqkv + 2 * d, D, ld3, M, D, M,
+                                             H, 1.0f, 2, stream);
     hipLaunchKernelGGL((k_blk_rope<true, float>), dim3((unsigned)((nrope + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, stream, b.dqkv, ld3, M, H, D, (const float2 *)b.rope);
     return group_backward(b.g[kGQkv], M, b.dqkv, ld3, b.n1, w[kGQkv], sg[kGQkv], clip_a[kGQkv],

@@ -131,6 +131,16 @@ def test_block_small(seed, M, d, f, H):
     check(p, target_of(p), f"block M={M} d={d} f={f} H={H}")
 
 
+@pytest.mark.parametrize("seed,M,d,f,H", [(7, 37, 384, 128, 64), (8, 1, 128, 128, 1),
+                                          (9, 67, 256, 128, 16), (10, 65, 128, 256, 64)])
+def test_block_head_widths(seed, M, d, f, H):
+    """The attention products at the edges of their tiles: head widths of 6,
+    128, 16 and 2 (rows that allow no 4-element loads among them), one token,
+    and token counts just past a 64-row tile that are no multiple of 4."""
+    p = calib_block_problem(seed, M, d, f, H)
+    check(p, target_of(p), f"block M={M} d={d} f={f} H={H}")
+
+
 def test_block_repeat_is_stable():
     """Two calls on one workspace give the same results (the float64
     scatter order aside)."""
