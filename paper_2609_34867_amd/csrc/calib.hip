@@ -38,6 +38,7 @@
 #include "q4_device.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace p4q {
 namespace {
@@ -451,6 +452,20 @@ __device__ __forceinline__ v16f mfma_bf16(uint4 a, uint4 b, v16f c) {
                                                    __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 
+// x of lane ^ m, m < 16, by DPP (4: mirrored halves of 8, mirrored quads)
+template <int m>
+__device__ __forceinline__ float lane_xor(float x) {
+    int v = __builtin_bit_cast(int, x);
+    if constexpr (m == 8) v = __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);       // row_ror:8
+    if constexpr (m == 4) {
+        v = __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true);                         // row_half_mirror
+        v = __builtin_amdgcn_update_dpp(0, v, 0x1B, 0xF, 0xF, true);                          // quad_perm 3,2,1,0
+    }
+    if constexpr (m == 2) v = __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);        // quad_perm 2,3,0,1
+    if constexpr (m == 1) v = __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);        // quad_perm 1,0,3,2
+    return __builtin_bit_cast(float, v);
+}
+
 // Epilogue per element (g = the contraction's value at (i, k), z' the
 // transformed input, code and inside bit as the quantizer decided them,
 // f = z'/s - code, taken only where inside):
@@ -661,8 +676,15 @@ __global__ __launch_bounds__(kThreads, 2) void k_calib_bwd(
     }
     // columns: the 32 values of each half-wave summed over its 32 lanes (the
     // i direction) by a halving exchange; lane l ends with value index l % 32
+    // (the distance-16 step as row swaps, the others through DPP)
 #pragma unroll
-    for (int m = 16; m >= 1; m >>= 1) {
+    for (int v = 0; v < 16; ++v) {
+        const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(colv[v]), __float_as_uint(colv[v + 16]),
+                                                        false, false);
+        colv[v] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
+    auto halve = [&](auto m_c) __attribute__((always_inline)) {
+        constexpr int m = decltype(m_c)::value;
         const bool up = (lane & m) != 0;
 #pragma unroll
         for (int v = 0; v < m; ++v) {
@@ -672,16 +694,22 @@ __global__ __launch_bounds__(kThreads, 2) void k_calib_bwd(
             asm volatile("" : "+v"(lo), "+v"(hi));
             const float send = up ? lo : hi;
             const float keep = up ? hi : lo;
-            colv[v] = keep + __shfl_xor(send, m);
+            colv[v] = keep + lane_xor<m>(send);
         }
-    }
+    };
+    halve(std::integral_constant<int, 8>{});
+    halve(std::integral_constant<int, 4>{});
+    halve(std::integral_constant<int, 2>{});
+    halve(std::integral_constant<int, 1>{});
     {
         const int v = r32, x = v >> 4, rg = (v >> 2) & 3, e = v & 3;
         colred[wi * BB + wk * 64 + 32 * x + 8 * rg + 4 * g2 + e] = colv[0];
     }
 #pragma unroll
     for (int y = 0; y < 2; ++y) {
-        const float r = rowv[y] + __shfl_xor(rowv[y], 32);
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(rowv[y]), __float_as_uint(rowv[y]),
+                                                        false, false);
+        const float r = __uint_as_float(p[0]) + __uint_as_float(p[1]);
         if (g2 == 0) rowred[wk * BB + wi * 64 + 32 * y + r32] = r;
     }
     __syncthreads();

@@ -83,3 +83,34 @@ def test_llava_next_b16_layer_sampled():
     first and last samples checked."""
     B, L, H = 16, 704, 32
     check(make_qkv(66, B, L, H, "fp16"), B, L, H, samples=[0, B - 1])
+
+
+@pytest.mark.parametrize("L,causal,dtype", [(63, True, "bf16"), (64, True, "fp16"), (65, True, "fp16"),
+                                            (192, False, "bf16"), (257, False, "fp16"), (450, True, "bf16")])
+def test_tile_edges(L, causal, dtype):
+    """Token counts at the edges of a 64-key tile and of a work-group's 128
+    queries (wavefronts without queries among them)."""
+    check(make_qkv(67 + L, 3, L, 2, dtype), 3, L, 2, causal=causal, dtype=dtype)
+
+
+def test_output_rows_without_16_byte_alignment():
+    """Output rows that allow 8-byte stores only: the same values, nothing
+    between the rows touched."""
+    B, L, H = 2, 130, 2
+    t = to_gpu(make_qkv(68, B, L, H, "fp16"))
+    HD = H * D
+    ref = p4q.attention_prefill(t[:, :HD], t[:, HD:2 * HD], t[:, 2 * HD:], B, H, True)
+    out = torch.zeros((B * L, HD + 12), dtype=torch.float16, device=t.device)
+    p4q.attention_prefill(t[:, :HD], t[:, HD:2 * HD], t[:, 2 * HD:], B, H, True, out=out[:, :HD])
+    assert torch.equal(out[:, :HD], ref)
+    assert torch.count_nonzero(out[:, HD:]) == 0
+
+
+def test_more_work_groups_than_one_grid_dimension():
+    """Over 2^20 work-groups (single-token samples): the output is v."""
+    B, H = 65535, 17
+    HD = H * D
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    t = torch.randn((B, 3 * HD), generator=g, device="cuda:0", dtype=torch.float16)
+    out = p4q.attention_prefill(t[:, :HD], t[:, HD:2 * HD], t[:, 2 * HD:], B, H, True)
+    assert torch.equal(out, t[:, 2 * HD:])
