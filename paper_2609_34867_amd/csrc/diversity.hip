@@ -197,6 +197,54 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t a) {
     return min(min(r0, r1), min(r2, r3));
 }
 
+// The value of lane ^ M as (smaller, larger) of the two, in both lanes.
+template <int M>
+__device__ __forceinline__ void pair_sorted(uint32_t x, uint32_t &lo, uint32_t &hi) {
+    uint32_t a = x, c;
+    if constexpr (M == 32) {
+        const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        a = p[0];
+        c = p[1];
+    } else if constexpr (M == 16) {
+        const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        a = p[0];
+        c = p[1];
+    } else if constexpr (M == 8) {
+        c = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xF, 0xF, false);     // row_ror:8
+    } else if constexpr (M == 4) {
+        c = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xF, 0xF, false);     // row_half_mirror
+        c = (uint32_t)__builtin_amdgcn_mov_dpp((int)c, 0x1B, 0xF, 0xF, false);      // quad_perm 3,2,1,0
+    } else if constexpr (M == 2) {
+        c = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, false);      // quad_perm 2,3,0,1
+    } else {
+        c = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, false);      // quad_perm 1,0,3,2
+    }
+    lo = min(a, c);
+    hi = max(a, c);
+}
+
+// ascending bitonic sort of one value per lane over the wavefront
+template <int SPAN, int M>
+__device__ __forceinline__ uint32_t bitonic_step(uint32_t x, int lane) {
+    uint32_t lo, hi;
+    pair_sorted<M>(x, lo, hi);
+    return (((lane & M) != 0) == ((lane & SPAN) != 0)) ? lo : hi;
+}
+template <int SPAN, int M>
+__device__ __forceinline__ uint32_t bitonic_merge(uint32_t x, int lane) {
+    x = bitonic_step<SPAN, M>(x, lane);
+    if constexpr (M > 1) x = bitonic_merge<SPAN, M / 2>(x, lane);
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_sort(uint32_t x, int lane) {
+    x = bitonic_merge<2, 1>(x, lane);
+    x = bitonic_merge<4, 2>(x, lane);
+    x = bitonic_merge<8, 4>(x, lane);
+    x = bitonic_merge<16, 8>(x, lane);
+    x = bitonic_merge<32, 16>(x, lane);
+    return bitonic_merge<64, 32>(x, lane);     // lane & 64 == 0: ascending
+}
+
 // order-preserving bits of an fp32 value (-0 below +0)
 __device__ __forceinline__ uint32_t ord32(float v) {
     const uint32_t u = __float_as_uint(v);
@@ -243,7 +291,10 @@ __global__ __launch_bounds__(NT) void k_div_greedy(const int32_t *__restrict__ G
     __shared__ int xi[NW];
     __shared__ __attribute__((aligned(16))) uint32_t wtot[16];
     __shared__ int32_t nvs[8192];                                  // Nv of the candidates
-    __shared__ uint32_t wlv[NW][kBatch + 1], wli[NW][kBatch + 1];  // per-wavefront smallest values, tokens
+    constexpr int kPub = 64 / NW;                                  // values published per wavefront
+    __shared__ __attribute__((aligned(16))) uint32_t wlv[64];      // the wavefronts' smallest values
+    __shared__ uint2 cand[64];                                     // (token, value) of the short list
+    __shared__ uint32_t ncand[2];                                  // its length
     __shared__ uint32_t vflag[2];                                  // verified list positions
 
     const int b = blockIdx.x, t = threadIdx.x, lane = t & 63;
@@ -399,7 +450,7 @@ __global__ __launch_bounds__(NT) void k_div_greedy(const int32_t *__restrict__ G
         }
     };
 
-    if (t == 0) { vflag[0] = 0; vflag[1] = 0; }
+    if (t == 0) { vflag[0] = 0; vflag[1] = 0; ncand[0] = 0; ncand[1] = 0; }
     __syncthreads();
     int par = 0;
     if (n0 == 0 && kd > 0) {
@@ -433,78 +484,83 @@ __global__ __launch_bounds__(NT) void k_div_greedy(const int32_t *__restrict__ G
     while (picks < kd) {
         // (1) selection on the order-preserving bits of vf (ties between
         //     equal values are left to the verification, which never accepts
-        //     them): per wavefront the kBatch + 1 smallest, then the same
-        //     extraction over the wavefronts' lists
-        uint32_t lv[kBatch + 1], li[kBatch + 1];
+        //     them).  Every wavefront sorts its lanes' minima and publishes the
+        //     kPub smallest; with T = the (kBatch + 1)-th smallest of the 64
+        //     published, at least kBatch + 1 candidates lie at or below T and
+        //     usually few more: they form the short list, which every
+        //     wavefront sorts by counting.  Taking the kBatch + 1 smallest one
+        //     after the other instead cost ~0.6 us per pick.
+        const int fb = nbatch & 1;            // alternating words: two barriers per selection
+        ++nbatch;
+        uint32_t ov[E];
+        uint32_t lm = kNone32;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            ov[e] = ((live >> e) & 1u) ? ord32(vf[e]) : kNone32;
+            lm = min(lm, ov[e]);
+        }
+        lm = wave_sort(lm, lane);
+        if (lane < kPub) wlv[wave * kPub + lane] = lm;
+        __syncthreads();
+        uint32_t T, v0;
         {
-            uint32_t ov[E];
+            const uint32_t mine = wlv[lane];
+            int le = 0;                       // published values <= mine
 #pragma unroll
-            for (int e = 0; e < E; ++e) ov[e] = ((live >> e) & 1u) ? ord32(vf[e]) : kNone32;
-            uint32_t ext = 0;
-            auto local_min = [&]() {
-                uint32_t m = kNone32;
-#pragma unroll
-                for (int e = 0; e < E; ++e) m = ((ext >> e) & 1u) ? m : min(m, ov[e]);
-                return m;
-            };
-            uint32_t lm = local_min();
-#pragma unroll
-            for (int r = 0; r <= kBatch; ++r) {
-                const uint32_t v = wave_min_u32(lm);
-                uint32_t tok = kNone32;
-                if (v != kNone32) {
-                    const int src = (int)__builtin_ctzll(__ballot(lm == v));      // lowest lane holding v
-                    int slot = 0;
-                    if (lane == src) {
-#pragma unroll
-                        for (int e = E - 1; e >= 0; --e)
-                            if (!((ext >> e) & 1u) && ov[e] == v) slot = e;
-                        ext |= 1u << slot;
-                        lm = local_min();
-                    }
-                    tok = (uint32_t)__shfl(slot * NT + t, src);
-                }
-                if (lane == 0) { wlv[wave][r] = v; wli[wave][r] = tok; }
+            for (int r = 0; r < 16; ++r) {
+                const uint4 w4 = reinterpret_cast<const uint4 *>(wlv)[r];
+                le += (int)(w4.x <= mine) + (int)(w4.y <= mine) + (int)(w4.z <= mine) + (int)(w4.w <= mine);
             }
-            __syncthreads();
-            constexpr int NE = NW * (kBatch + 1);
-            constexpr int PER = (NE + 63) / 64;
-            uint32_t av[PER], ai[PER];
+            v0 = wave_min_u32(mine);
+            T = min(wave_min_u32(le > kBatch ? mine : kNone32), kNone32 - 1);
+        }
+        if (v0 == kNone32) break;             // no candidate left (not reached for kd <= N - n0)
+        {
+            int base = 0, off[E];
 #pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int q = lane + 64 * u;
-                av[u] = q < NE ? wlv[q / (kBatch + 1)][q % (kBatch + 1)] : kNone32;
-                ai[u] = q < NE ? wli[q / (kBatch + 1)][q % (kBatch + 1)] : kNone32;
+            for (int e = 0; e < E; ++e) {
+                const uint64_t mk = __ballot(ov[e] <= T);
+                off[e] = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0));
+                base += __builtin_popcountll(mk);
             }
+            if (base > 0) {                   // wave-uniform
+                int at = 0;
+                if (lane == 0) at = (int)atomicAdd(&ncand[fb], (uint32_t)base);
+                at = __builtin_amdgcn_readfirstlane(at);
 #pragma unroll
-            for (int r = 0; r <= kBatch; ++r) {
-                uint32_t m = kNone32;
-#pragma unroll
-                for (int u = 0; u < PER; ++u) m = min(m, av[u]);
-                const uint32_t v = wave_min_u32(m);
-                uint32_t tok = kNone32;
-                if (v != kNone32) {
-                    const int src = (int)__builtin_ctzll(__ballot(m == v));
-                    uint32_t mine = kNone32;
-                    if (lane == src) {
-                        bool done = false;
-#pragma unroll
-                        for (int u = 0; u < PER; ++u)
-                            if (!done && av[u] == v) { mine = ai[u]; av[u] = kNone32; done = true; }
-                    }
-                    tok = (uint32_t)__shfl((int)mine, src);
-                }
-                lv[r] = v;
-                li[r] = tok;
+                for (int e = 0; e < E; ++e)
+                    if (ov[e] <= T && at + off[e] < 64) cand[at + off[e]] = make_uint2((uint32_t)(e * NT + t), ov[e]);
             }
         }
-        if (lv[0] == kNone32) break;          // no candidate left (not reached for kd <= N - n0)
-        // (2) the head: exact unless it is clear of the runner-up
-        const bool head_clear = lv[1] == kNone32 || lv[1] - lv[0] > kUlpTol;
-        int nb = head_clear ? min(kBatch, kd - picks) : 1;
+        __syncthreads();
+        const int n = __builtin_amdgcn_readfirstlane((int)ncand[fb]);
+        if (t == 0) ncand[fb ^ 1] = 0;        // the next selection's word
+        // a longer list (many close values, in few wavefronts): one pick, the
+        // exact minimum of the candidates near the smallest value
+        const bool listed = n <= 64;
+        uint32_t lv[kBatch + 1];
         int c[kBatch];
+        {
+            const uint2 mine = lane < n ? cand[lane] : make_uint2(kNone32, kNone32);
+            const uint64_t key = ((uint64_t)mine.y << 32) | mine.x;
+            int rank = lane < n ? 0 : lane;
+            if (listed)
+                for (int j = 0; j < n; ++j) {
+                    const uint2 o = cand[j];
+                    const uint64_t ok = ((uint64_t)o.y << 32) | o.x;
+                    rank += (int)(lane < n && ok < key);
+                }
+            const uint32_t sv = (uint32_t)__builtin_amdgcn_ds_permute(rank * 4, (int)mine.y);
+            const uint32_t si = (uint32_t)__builtin_amdgcn_ds_permute(rank * 4, (int)mine.x);
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) c[j] = (int)li[j];
+            for (int r = 0; r <= kBatch; ++r) lv[r] = __builtin_amdgcn_readlane((int)sv, r);
+#pragma unroll
+            for (int r = 0; r < kBatch; ++r) c[r] = __builtin_amdgcn_readlane((int)si, r);
+        }
+        if (!listed) lv[0] = v0;
+        // (2) the head: exact unless it is clear of the runner-up
+        const bool head_clear = listed && (lv[1] == kNone32 || lv[1] - lv[0] > kUlpTol);
+        int nb = head_clear ? min(kBatch, kd - picks) : 1;
         if (!head_clear) c[0] = exact_min(lv[0] + kUlpTol);
         for (int j = 1; j < kBatch; ++j)      // the list may run out
             if (j < nb && lv[j] == kNone32) nb = j;
@@ -519,30 +575,34 @@ __global__ __launch_bounds__(NT) void k_div_greedy(const int32_t *__restrict__ G
                 invb[j] = nvb > 0 ? 1.0f / (float)nvb : 0.0f;
             }
         }
-        // (4) verify c_1 .. c_{nb-1}: the owner of c_j raises its value by the
-        // rows of c_0 .. c_{j-1} and compares with the value of c_{j+1}
-        const int fb = nbatch & 1;            // alternating flag word: one barrier per batch
-        ++nbatch;
-        if (nb > 1) {
+        // (4) verify c_1 .. c_{nb-1}: thread 16 j + k raises the value of c_j
+        // by the row of c_k, k < j; the 16 threads' maximum is compared with
+        // the value of c_{j+1}
+        if (nb > 1 && t < 16 * kBatch) {
+            const int j = t >> 4, k = t & 15;
+            int cj = c[0], ck = c[0];
+            uint32_t vj = lv[0], vnext = lv[1];
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int i = e * NT + t;
-#pragma unroll
-                for (int j = 1; j < kBatch; ++j) {
-                    if (j < nb && i == c[j] && ((live >> e) & 1u)) {
-                        float v = vf[e];
-#pragma unroll
-                        for (int k2 = 0; k2 < kBatch; ++k2) {
-                            if (k2 < j) {
-                                const float df = (float)Drow[k2][e];
-                                v = __builtin_fmaxf(v, ((df * __builtin_fabsf(df)) * inv[e]) * invb[k2]);
-                            }
-                        }
-                        if (lv[j + 1] == kNone32 || (int64_t)ord32(v) + (int64_t)kUlpTol < (int64_t)lv[j + 1])
-                            atomicOr(&vflag[fb], 1u << j);
-                    }
-                }
+            for (int r = 1; r < kBatch; ++r) {
+                cj = j == r ? c[r] : cj;
+                ck = k == r ? c[r] : ck;
+                vj = j == r ? lv[r] : vj;
+                vnext = j == r ? lv[r + 1] : vnext;
             }
+            const bool on = j < nb && k < j;
+            const uint32_t at = on ? ((uint32_t)ck * (uint32_t)N + (uint32_t)cj) * 4u : 0x80000000u;
+            const float df = (float)(int32_t)__builtin_amdgcn_raw_buffer_load_b32(gres, at, 0, 0);
+            const int32_t nj = on ? nvs[cj] : 0, nk = on ? nvs[ck] : 0;
+            const float ij = nj > 0 ? 1.0f / (float)nj : 0.0f, ik = nk > 0 ? 1.0f / (float)nk : 0.0f;
+            float v = on ? ((df * __builtin_fabsf(df)) * ij) * ik : -__builtin_huge_valf();
+            v = __builtin_fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false)));
+            v = __builtin_fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, false)));
+            v = __builtin_fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x141, 0xF, 0xF, false)));
+            v = __builtin_fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xF, 0xF, false)));
+            const uint32_t raised = max(vj, ord32(v));
+            const bool ok = j > 0 && j < nb &&
+                            (vnext == kNone32 || (int64_t)raised + (int64_t)kUlpTol < (int64_t)vnext);
+            if (k == 0 && ok) atomicOr(&vflag[fb], 1u << j);
         }
         __syncthreads();
         const uint32_t fl = vflag[fb];

@@ -102,6 +102,18 @@ def test_gram_on_the_large_tile_kernel():
     check(vis, con, cls, text, 300, 90, 60)
 
 
+@pytest.mark.parametrize("N,K", [(700, 300), (2300, 260), (8192, 90)])
+def test_many_close_candidates(N, K):
+    """More candidates near the smallest value than the greedy's short list
+    holds: a run of zero rows (equal values, in few wavefronts), a run of near
+    copies of one row, and a stage that takes nearly every token left."""
+    vis, con, cls, text = synth(27 + N, 1, N, 128, 2, 2)
+    vis[0, 64:230] = 0
+    near = vis[0, 300:301].astype(np.float32) + 0.02 * np.arange(100, dtype=np.float32)[:, None]
+    vis[0, 320:420] = near.astype(vis.dtype)
+    check(vis, con, cls, text, K, 5, 3)
+
+
 def test_bf16_clip_no_text():
     vis, con, cls, _ = synth(25, 2, 777, 768, 3, 0, dtype="bf16")
     check(vis, con, cls, None, 150, 45, 30, dtype="bf16")
