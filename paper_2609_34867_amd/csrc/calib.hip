@@ -346,21 +346,17 @@ __global__ __launch_bounds__(kThreads) void k_codes_bf16t_wide(const uint8_t *__
 
 // ---------------------------------------------------------------------------
 // 4. Residual, bf16 contraction operands and loss partials.  64 x 64 tiles;
-//    grid (N / 64, Mp / 64).  The grid also clears the float64 scatter
-//    targets of k_calib_rows.
+//    grid (N / 64, Mp / 64).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void k_calib_residual(
     const int32_t *__restrict__ acc, const float *__restrict__ sa, const float *__restrict__ sw,
     const float *__restrict__ T, int64_t ldt, int M, int N, int Mp, uint16_t *__restrict__ P1,
-    uint16_t *__restrict__ P2T, double *__restrict__ loss_part, double *__restrict__ corr,
-    int ncorr) {
+    uint16_t *__restrict__ P2T, double *__restrict__ loss_part) {
     __shared__ __attribute__((aligned(16))) uint16_t tr[64 * 72];   // [n][m] bf16(R sA)
     __shared__ double red[kThreads / 64];
     const int t = threadIdx.x;
     const int n0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
     const int bid = blockIdx.y * gridDim.x + blockIdx.x;
-    const int nb = gridDim.x * gridDim.y;
-    for (int i = bid * kThreads + t; i < ncorr; i += nb * kThreads) corr[i] = 0.0;
 
     const int cn = 4 * (t & 15);
     const float4 swv = *reinterpret_cast<const float4 *>(sw + n0 + cn);
@@ -755,18 +751,18 @@ __device__ __forceinline__ double group_total(double v, double *part) {
 }
 
 constexpr int kRowsA = 16;     // activation rows per block (their slots are many)
-constexpr int kRowsW = 64;     // weight rows, columns per block
+constexpr int kRowsW = 64;     // weight rows per block
+constexpr int kColsB = 16;     // columns per block
 
-// 6. Rows: g_s, the clip gradients, and the row maximum's share scattered
-//    to its column.  Blocks [0, nbA) hold activation rows, the rest weight
-//    rows.
+// 6. Rows: g_s, the clip gradients, and the row maximum's share (which the
+//    column kernel adds to its column).  Blocks [0, nbA) hold activation rows,
+//    the rest weight rows.
 __global__ __launch_bounds__(kThreads) void k_calib_rows(
     const float *__restrict__ rowA, int nsA, int M, const float *__restrict__ sA,
-    const float *__restrict__ aA, const int32_t *__restrict__ kA, float clip_a,
+    const float *__restrict__ aA, float clip_a,
     const float *__restrict__ rowW, int nsW, int N, const float *__restrict__ sW,
-    const float *__restrict__ aW, const int32_t *__restrict__ kW,
-    const float *__restrict__ clip_w, int nbA, double scale, double *__restrict__ corrA,
-    double *__restrict__ corrW, double *__restrict__ dclipa_part,
+    const float *__restrict__ aW, const float *__restrict__ clip_w, int nbA, double scale,
+    double *__restrict__ shareA, double *__restrict__ shareW, double *__restrict__ dclipa_part,
     float *__restrict__ grad_clip_w) {
     __shared__ double part[kThreads];
     const int t = threadIdx.x;
@@ -778,7 +774,7 @@ __global__ __launch_bounds__(kThreads) void k_calib_rows(
             double v = 0.0;
             if (t < kRowsA && m < M) {
                 const double a = (double)aA[m];
-                if (sA[m] != 0.0f) atomicAdd(&corrA[kA[m]], gs * (double)clip_a * a / 7.0);
+                shareA[m] = (sA[m] != 0.0f) ? gs * (double)clip_a * a / 7.0 : 0.0;
                 v = gs * a / 7.0;
             }
 #pragma unroll
@@ -791,28 +787,72 @@ __global__ __launch_bounds__(kThreads) void k_calib_rows(
             n < N ? slot_sum<kThreads / kRowsW>(rowW + n, nsW, N, t / kRowsW) : 0.0, part);
         if (t < kRowsW && n < N) {
             const double a = (double)aW[n];
-            if (sW[n] != 0.0f) atomicAdd(&corrW[kW[n]], gs * (double)clip_w[n] * a / 7.0);
+            shareW[n] = (sW[n] != 0.0f) ? gs * (double)clip_w[n] * a / 7.0 : 0.0;
             grad_clip_w[n] = (float)(scale * gs * a / 7.0);
         }
     }
 }
 
-// 7. Columns: d sigma; block 0 also reduces the loss and d clip_a.
+// the shares of the rows whose maximum lies in [k0, k0 + kColsB), added up in
+// LDS per column.  Every share is loaded with its column: loaded only on a
+// match, a block whose columns hold many maxima waits out one load after the
+// other (the column kernel: 18 us instead of 8.5).
+__device__ __forceinline__ void add_shares(const int32_t *__restrict__ kmax,
+                                           const double *__restrict__ share, int rows, int k0,
+                                           double *acc) {
+    auto add = [&](int k, double v) __attribute__((always_inline)) {
+        if ((unsigned)(k - k0) < (unsigned)kColsB) atomicAdd(&acc[k - k0], v);
+    };
+    constexpr int U = 8;                        // loads in flight
+    const int r2 = rows >> 1;
+    for (int i0 = threadIdx.x; i0 < r2; i0 += U * kThreads) {
+        int2 k[U];
+        double2 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(i0 + u * kThreads, r2 - 1);
+            k[u] = reinterpret_cast<const int2 *>(kmax)[i];
+            v[u] = reinterpret_cast<const double2 *>(share)[i];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i0 + u * kThreads < r2) {
+                add(k[u].x, v[u].x);
+                add(k[u].y, v[u].y);
+            }
+        }
+    }
+    if (threadIdx.x == 0 && (rows & 1)) add(kmax[rows - 1], share[rows - 1]);
+}
+
+// 7. Columns: d sigma; block 0 also reduces the loss and d clip_a.  Every
+//    block reads all rows' shares and their columns (12 bytes per row, from L2) and
+//    takes the shares of its own columns: scattered by the row kernel with
+//    atomics in memory (compare-and-swap loops on fp64, on few addresses) they
+//    took most of its 18 us at 12288 + 384 rows (now 4.8 us; this kernel, K =
+//    4096 with 111 slots: 6.5 us before, 8.5 us with the shares).  16 columns a
+//    block instead of 64 put enough loads in flight.
 __global__ __launch_bounds__(kThreads) void k_calib_cols(
     const float *__restrict__ colA, int nslA, const float *__restrict__ colW, int nslW,
-    const double *__restrict__ corrA, const double *__restrict__ corrW,
+    const int32_t *__restrict__ kA, const double *__restrict__ shareA, int M,
+    const int32_t *__restrict__ kW, const double *__restrict__ shareW, int N,
     const float *__restrict__ sigma, int K, double scale, float *__restrict__ grad_sigma,
     const double *__restrict__ loss_part, int nloss, double inv_mn, float *__restrict__ loss,
     const double *__restrict__ dclipa_part, int nbA, float *__restrict__ grad_clip_a) {
     __shared__ double part[kThreads];
     __shared__ double red[kThreads / 64];
-    const int t = threadIdx.x, c = t % kRowsW, g = t / kRowsW;
-    const int k = blockIdx.x * kRowsW + c;      // K % 64 == 0
-    const double cx = group_total<kRowsW>(slot_sum<kThreads / kRowsW>(colA + k, nslA, K, g), part);
+    __shared__ double corr[2][kColsB];
+    const int t = threadIdx.x, c = t % kColsB, g = t / kColsB;
+    const int k0 = blockIdx.x * kColsB, k = k0 + c;             // K % 64 == 0
+    if (t < 2 * kColsB) corr[t / kColsB][t % kColsB] = 0.0;
     __syncthreads();
-    const double cw = group_total<kRowsW>(slot_sum<kThreads / kRowsW>(colW + k, nslW, K, g), part);
-    if (t < kRowsW)
-        grad_sigma[k] = (float)(scale * ((cw + corrW[k]) - (cx + corrA[k])) / (double)sigma[k]);
+    add_shares(kA, shareA, M, k0, corr[0]);
+    add_shares(kW, shareW, N, k0, corr[1]);
+    const double cx = group_total<kColsB>(slot_sum<kThreads / kColsB>(colA + k, nslA, K, g), part);
+    __syncthreads();
+    const double cw = group_total<kColsB>(slot_sum<kThreads / kColsB>(colW + k, nslW, K, g), part);
+    if (t < kColsB)
+        grad_sigma[k] = (float)(scale * ((cw + corr[1][t]) - (cx + corr[0][t])) / (double)sigma[k]);
     if (blockIdx.x == 0) {
         double l = 0.0;
         for (int i = t; i < nloss; i += kThreads) l += loss_part[i];
@@ -835,6 +875,7 @@ inline size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct CalibPlan {
     int Mp, nsA, jsA, nsW, jsW, nbA, nloss, tilesMA, tilesNW;
+    int capA, capW;     // splits that the workspace has room for (>= nsA, nsW)
 };
 
 CalibPlan calib_plan(int M, int N, int K) {
@@ -843,15 +884,29 @@ CalibPlan calib_plan(int M, int N, int K) {
     const int kt = K / BB;
     p.tilesMA = (M + BB - 1) / BB;
     p.tilesNW = (N + BB - 1) / BB;
-    auto splits = [](int tiles, int J, int &ns, int &js) {
-        // about two work-groups per CU of 256, at least 4 stages per split
-        int want = (512 + tiles - 1) / tiles;
-        want = std::max(1, std::min(want, J / (4 * BJ)));
-        js = ((J + want - 1) / want + BJ - 1) / BJ * BJ;
+    auto splits = [](int tiles, int J, int &ns, int &js, int &cap) {
+        // Two work-groups fit on each of 256 CUs: up to as many splits as fill
+        // them, at least 4 stages per split, and of those the number with the
+        // shortest rounds of work-groups (stages + 10 for the epilogue; a last
+        // round of at most one work-group per CU takes 0.7 of a full one).
+        // 96 tiles of 192 stages: 5 splits (480 work-groups) 47 us, 6 splits
+        // (576) 62 us; 258 tiles of 64 stages: 2 splits 83 us, 3 splits 92 us.
+        const int top = std::max(1, std::min((512 + tiles - 1) / tiles, J / (4 * BJ)));
+        int64_t best = INT64_MAX;
+        for (int n = 1; n <= top; ++n) {
+            const int j = ((J + n - 1) / n + BJ - 1) / BJ * BJ;
+            cap = (J + j - 1) / j;              // grows with n
+            const int64_t wgs = (int64_t)tiles * cap, left = wgs % 512;
+            const int64_t cost = (10 * (wgs / 512) + (left == 0 ? 0 : left <= 256 ? 7 : 10)) * (j / BJ + 10);
+            if (cost < best) {
+                best = cost;
+                js = j;
+            }
+        }
         ns = (J + js - 1) / js;
     };
-    splits(p.tilesMA * kt, N, p.nsA, p.jsA);
-    splits(p.tilesNW * kt, p.Mp, p.nsW, p.jsW);
+    splits(p.tilesMA * kt, N, p.nsA, p.jsA, p.capA);
+    splits(p.tilesNW * kt, p.Mp, p.nsW, p.jsW, p.capW);
     p.nbA = (M + kRowsA - 1) / kRowsA;
     p.nloss = (N / 64) * (p.Mp / 64);
     return p;
@@ -865,7 +920,7 @@ struct CalibWs {
     float *xprime;
     uint8_t *insA, *insW;
     int32_t *acc;
-    double *loss_part, *corr, *dclipa_part;
+    double *loss_part, *shareA, *shareW, *dclipa_part;
     float *rowA, *colA, *rowW, *colW;
 };
 
@@ -895,12 +950,13 @@ size_t calib_carve(const CalibPlan &p, int M, int N, int K, uint8_t *base, Calib
     c.P1 = reinterpret_cast<uint16_t *>(take((size_t)M * N * 2));
     c.P2T = reinterpret_cast<uint16_t *>(take((size_t)N * p.Mp * 2));
     c.loss_part = reinterpret_cast<double *>(take((size_t)p.nloss * 8));
-    c.corr = reinterpret_cast<double *>(take((size_t)2 * K * 8));
+    c.shareA = reinterpret_cast<double *>(take((size_t)M * 8));
+    c.shareW = reinterpret_cast<double *>(take((size_t)N * 8));
     c.dclipa_part = reinterpret_cast<double *>(take((size_t)p.nbA * 8));
-    c.rowA = reinterpret_cast<float *>(take((size_t)kt * p.nsA * M * 4));
-    c.colA = reinterpret_cast<float *>(take((size_t)p.tilesMA * p.nsA * K * 4));
-    c.rowW = reinterpret_cast<float *>(take((size_t)kt * p.nsW * N * 4));
-    c.colW = reinterpret_cast<float *>(take((size_t)p.tilesNW * p.nsW * K * 4));
+    c.rowA = reinterpret_cast<float *>(take((size_t)kt * p.capA * M * 4));
+    c.colA = reinterpret_cast<float *>(take((size_t)p.tilesMA * p.capA * K * 4));
+    c.rowW = reinterpret_cast<float *>(take((size_t)kt * p.capW * N * 4));
+    c.colW = reinterpret_cast<float *>(take((size_t)p.tilesNW * p.capW * K * 4));
     if (w) *w = c;
     return off;
 }
@@ -937,8 +993,7 @@ hipError_t calib_typed(int M, int N, int K, const void *x, int64_t ldx, const vo
         return e;
     // 4. residual
     hipLaunchKernelGGL(k_calib_residual, dim3(N / 64, p.Mp / 64), dim3(kThreads), 0, stream,
-                       c.acc, c.sA, c.sW, target, ldt, M, N, p.Mp, c.P1, c.P2T, c.loss_part,
-                       c.corr, 2 * K);
+                       c.acc, c.sA, c.sW, target, ldt, M, N, p.Mp, c.P1, c.P2T, c.loss_part);
     // 5. backward contractions with fused reductions
     hipLaunchKernelGGL((k_calib_bwd<BF16, true>), dim3(K / BB, p.tilesMA, p.nsA),
                        dim3(kThreads), 0, stream, c.P1, (int64_t)N, c.CwT, (int64_t)N, M, N,
@@ -953,12 +1008,12 @@ hipError_t calib_typed(int M, int N, int K, const void *x, int64_t ldx, const vo
     const double scale = 2.0 / ((double)M * (double)N);
     const int nbW = (N + kRowsW - 1) / kRowsW;
     hipLaunchKernelGGL(k_calib_rows, dim3(p.nbA + nbW), dim3(kThreads), 0, stream, c.rowA,
-                       (K / BB) * p.nsA, M, c.sA, c.aA, c.kA, clip_a, c.rowW, (K / BB) * p.nsW,
-                       N, c.sW, c.aW, c.kW, clip_w, p.nbA, scale, c.corr, c.corr + K,
-                       c.dclipa_part, grad_clip_w);
-    hipLaunchKernelGGL(k_calib_cols, dim3(K / kRowsW), dim3(kThreads), 0,
-                       stream, c.colA, p.tilesMA * p.nsA, c.colW, p.tilesNW * p.nsW, c.corr,
-                       c.corr + K, sigma, K, scale, grad_sigma, c.loss_part, p.nloss,
+                       (K / BB) * p.nsA, M, c.sA, c.aA, clip_a, c.rowW, (K / BB) * p.nsW, N,
+                       c.sW, c.aW, clip_w, p.nbA, scale, c.shareA, c.shareW, c.dclipa_part,
+                       grad_clip_w);
+    hipLaunchKernelGGL(k_calib_cols, dim3(K / kColsB), dim3(kThreads), 0,
+                       stream, c.colA, p.tilesMA * p.nsA, c.colW, p.tilesNW * p.nsW, c.kA, c.shareA,
+                       M, c.kW, c.shareW, N, sigma, K, scale, grad_sigma, c.loss_part, p.nloss,
                        1.0 / ((double)M * (double)N), loss, c.dclipa_part, p.nbA, grad_clip_a);
     return hipGetLastError();
 }
@@ -1330,13 +1385,10 @@ __global__ __launch_bounds__(kThreads) void k_blk_out(const uint16_t *__restrict
 __global__ __launch_bounds__(kThreads) void k_blk_upstream(
     const float *__restrict__ G, int64_t ldg, const float *__restrict__ sa,
     const float *__restrict__ sw, int M, int N, int Mp, uint16_t *__restrict__ P1,
-    uint16_t *__restrict__ P2T, double *__restrict__ corr, int ncorr) {
+    uint16_t *__restrict__ P2T) {
     __shared__ __attribute__((aligned(16))) uint16_t tr[64 * 72];
     const int t = threadIdx.x;
     const int n0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
-    const int bid = blockIdx.y * gridDim.x + blockIdx.x;
-    const int nb = gridDim.x * gridDim.y;
-    for (int i = bid * kThreads + t; i < ncorr; i += nb * kThreads) corr[i] = 0.0;
     const int cn = 4 * (t & 15);
     const float4 swv = *reinterpret_cast<const float4 *>(sw + n0 + cn);
     const float swa[4] = {swv.x, swv.y, swv.z, swv.w};
@@ -1455,7 +1507,7 @@ size_t block_carve(int M, int d, int f, int H, uint8_t *base, BlockWs *w) {
         const size_t cb = calib_carve(g.p, M, g.N, g.K, nullptr, nullptr);
         uint8_t *cbase = take(cb);
         calib_carve(g.p, M, g.N, g.K, cbase, &g.c);
-        g.gpart = g.dx ? reinterpret_cast<float *>(take((size_t)g.p.nsA * M * g.K * 4)) : nullptr;
+        g.gpart = g.dx ? reinterpret_cast<float *>(take((size_t)g.p.capA * M * g.K * 4)) : nullptr;
     }
     const size_t Md = (size_t)M * d, Mf = (size_t)M * f, HMM = (size_t)H * M * score_ld(M);
     auto h16 = [&](size_t n) { return reinterpret_cast<uint16_t *>(take(n * 2)); };
@@ -1515,7 +1567,7 @@ hipError_t group_backward(BlockGroup &g, int M, const float *G, int64_t ldg, con
     const CalibPlan &p = g.p;
     const int N = g.N, K = g.K;
     hipLaunchKernelGGL(k_blk_upstream, dim3(N / 64, p.Mp / 64), dim3(kThreads), 0, stream, G, ldg,
-                       c.sA, c.sW, M, N, p.Mp, c.P1, c.P2T, c.corr, 2 * K);
+                       c.sA, c.sW, M, N, p.Mp, c.P1, c.P2T);
     hipLaunchKernelGGL((k_calib_bwd<false, true>), dim3(K / BB, p.tilesMA, p.nsA),
                        dim3(kThreads), 0, stream, c.P1, (int64_t)N, c.CwT, (int64_t)N, M, N, p.jsA,
                        X, (int64_t)K, c.xprime, c.codesA, c.insA, sigma, c.sA, K, c.rowA, c.colA,
@@ -1526,11 +1578,11 @@ hipError_t group_backward(BlockGroup &g, int M, const float *G, int64_t ldg, con
                        c.codesW, c.insW, sigma, c.sW, K, c.rowW, c.colW, nullptr);
     const int nbW = (N + kRowsW - 1) / kRowsW;
     hipLaunchKernelGGL(k_calib_rows, dim3(p.nbA + nbW), dim3(kThreads), 0, stream, c.rowA,
-                       (K / BB) * p.nsA, M, c.sA, c.aA, c.kA, clip_a, c.rowW, (K / BB) * p.nsW, N,
-                       c.sW, c.aW, c.kW, clip_w, p.nbA, 1.0, c.corr, c.corr + K, c.dclipa_part,
-                       grad_clip_w);
-    hipLaunchKernelGGL(k_calib_cols, dim3(K / kRowsW), dim3(kThreads), 0, stream, c.colA,
-                       p.tilesMA * p.nsA, c.colW, p.tilesNW * p.nsW, c.corr, c.corr + K, sigma, K,
+                       (K / BB) * p.nsA, M, c.sA, c.aA, clip_a, c.rowW, (K / BB) * p.nsW, N, c.sW,
+                       c.aW, clip_w, p.nbA, 1.0, c.shareA, c.shareW, c.dclipa_part, grad_clip_w);
+    hipLaunchKernelGGL(k_calib_cols, dim3(K / kColsB), dim3(kThreads), 0, stream, c.colA,
+                       p.tilesMA * p.nsA, c.colW, p.tilesNW * p.nsW, c.kA, c.shareA, M, c.kW, c.shareW,
+                       N, sigma, K,
                        1.0, grad_sigma, loss_part, nloss, inv_md, loss, c.dclipa_part, p.nbA,
                        grad_clip_a);
     if (dX)

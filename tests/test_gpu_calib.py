@@ -181,3 +181,16 @@ def test_calib_heavy_clamping():
     # the activations' outlier channels set their row maxima, so fewer of
     # their values saturate than the weights'
     assert np.mean(np.abs(ref["a_codes"]) >= 7) > 0.02 and np.mean(np.abs(ref["w_codes"]) >= 7) > 0.3
+
+
+@pytest.mark.parametrize("M,N,col", [(1, 64, 0), (77, 64, 15), (130, 2112, 16), (259, 192, 255)])
+def test_calib_one_column_holds_every_maximum(M, N, col):
+    """Every row's maximum in one column (first and last of a block of 16
+    columns): all shares through the scales meet there; odd and single rows,
+    more weight rows than one pass over them loads."""
+    p = calib_problem(95 + M, M, N, 256)
+    p.x[:, col] = np.float16(100.0)
+    p.w[:, col] = np.float16(0.25)
+    p.sigma[col] = 1.0
+    p.target[:] = p.x.astype(np.float64) @ p.w.astype(np.float64).T
+    compare(p, run_calib(p))
