@@ -114,6 +114,31 @@ def test_many_close_candidates(N, K):
     check(vis, con, cls, text, K, 5, 3)
 
 
+@pytest.mark.parametrize("N,kind", [(1, "equal"), (2880, "equal"), (2880, "outlier"), (2049, "signs"),
+                                    (700, "adjacent"), (1300, "extremes")])
+def test_saliency_score_ranges(N, kind):
+    """Score distributions against the range that the first digit of the
+    saliency selection divides: no range at all, one score that pushes all
+    others (more than the direct ranking takes) into one bucket, both signs
+    and zeros, a range of fewer values than buckets, the whole fp32 range."""
+    vis, con, cls, text = synth(31 + N, 1, N, 64, 1, 1)
+    g = np.random.default_rng(N)
+    if kind == "equal":
+        cls[:] = 0.25
+    elif kind == "outlier":
+        cls[0, N // 2] = 1e30
+    elif kind == "signs":
+        cls[0] = g.standard_normal(N)
+        cls[0, ::7], cls[0, 3::7] = 0.0, -0.0
+    elif kind == "adjacent":
+        cls[0] = (np.float32(1.0).view(np.uint32) + g.integers(0, 900, N).astype(np.uint32)).view(np.float32)
+    else:
+        cls[0, :4] = [np.finfo(np.float32).max, -np.finfo(np.float32).max, 1e-45, -1e-45]
+    K = min(N, 400)
+    check(vis, con, cls, text, K, 0, K)
+    check(vis, con, cls, text, K, K // 4, K // 2)
+
+
 def test_bf16_clip_no_text():
     vis, con, cls, _ = synth(25, 2, 777, 768, 3, 0, dtype="bf16")
     check(vis, con, cls, None, 150, 45, 30, dtype="bf16")
