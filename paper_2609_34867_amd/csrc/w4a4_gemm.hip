@@ -17,6 +17,7 @@
 #include "p4q_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace p4q {
 namespace {
@@ -404,20 +405,23 @@ template <int BMT> constexpr int l_stages() { return BMT == 256 ? 3 : kMidStages
 template <int BMT> constexpr int l_stage() { return (BMT + L_BN) * BKB; }   // packed codes
 template <int BMT> constexpr int l_scale_off() { return l_stages<BMT>() * l_stage<BMT>(); }
 // Gram mode (M == N, A == W): only tiles holding an entry on or above the
-// diagonal, i.e. tn >= 2 tm for 256 x 128 tiles; row tm of tiles holds
-// tiles_n - 2 tm of them.  Same XCD-contiguous dealing as xcd_logical.
+// diagonal; row tm of BM x 128 tiles starts at tn = tm BM / 128.  Same
+// XCD-contiguous dealing as xcd_logical.
+template <int BMT>
+__host__ __device__ __forceinline__ int gram_first(int tm) { return tm * BMT / L_BN; }
+template <int BMT>
 __device__ __forceinline__ void gram_tile_coords(int wg, int total, int tiles_n, int &tm, int &tn) {
     const int q = total / kXcds, r = total % kXcds;
     const int x = wg % kXcds, i = wg / kXcds;
     int logical = (x < r) ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
     tm = 0;
     while (true) {
-        const int c = max(0, tiles_n - 2 * tm);
+        const int c = max(0, tiles_n - gram_first<BMT>(tm));
         if (logical < c) break;
         logical -= c;
         ++tm;
     }
-    tn = 2 * tm + logical;
+    tn = gram_first<BMT>(tm) + logical;
 }
 
 // Two adjacent packed words: the low nibbles of both move up by one 64-bit
@@ -451,7 +455,7 @@ __global__ __launch_bounds__(256, BMT == 64 ? 4 : 2) void k_w4a4_gemm_2cu(const 
                                                           int32_t *__restrict__ part, int tdp,
                                                           int nsplit,
                                                           uint32_t *__restrict__ arrivals) {
-    static_assert(BMT == 256 || ((BMT == 128 || BMT == 64) && YOUT), "tile height");
+    static_assert(BMT == 256 || BMT == 128 || BMT == 64, "tile height");
     static_assert(!SPLIT || YOUT, "split-K is a mode of the y-output kernel");
     constexpr int L_STAGE = l_stage<BMT>();
     constexpr int AI = BMT / 64;          // A DMA instructions per wavefront and stage
@@ -484,7 +488,7 @@ __global__ __launch_bounds__(256, BMT == 64 ? 4 : 2) void k_w4a4_gemm_2cu(const 
         }
         grouped_tile(logical, tiles_m, tiles_n, tm, tn);
     } else {
-        gram_tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
+        gram_tile_coords<BMT>(blockIdx.x, tiles_m, tiles_n, tm, tn);
     }
     const int m0 = tm * BMT, n0 = tn * L_BN;
     // this block's k-tiles [kbeg, kbeg + ktiles); the launch makes every split non-empty
@@ -680,7 +684,60 @@ __global__ __launch_bounds__(256, BMT == 64 ? 4 : 2) void k_w4a4_gemm_2cu(const 
         }
     }
 
-    if constexpr (!YOUT) {      // Gram mode: int32 accumulators only
+    if constexpr (!YOUT) {
+        // Gram mode: the int32 tile goes to [m][n] and, transposed, to [n][m].
+        // Rows of whole 16-byte units (N % 4 == 0) pass through the wavefront's
+        // own part of LDS and leave as whole rows of its BMT / 2 x 64 part (a tile
+        // on the diagonal writes some entries twice, with the same value).
+        // Stores bound the epilogue: 16 x 2880 tokens (531 MB) took 313 us with
+        // 64-byte pieces straight from the accumulators, take 266 us so, and
+        // 203 us without any.  Other rows go straight from the accumulators:
+        // with one 4-byte store per lane the way through LDS does not pay
+        // (1 x 2333 tokens: 52.7 against 56.8 us).
+        if ((N & 3) == 0 && (reinterpret_cast<uintptr_t>(acc_out) & 15) == 0) {
+            constexpr int kW = BMT / 2;                 // rows m of the wavefront
+            constexpr int kTRow = 4 * kW + 16;          // a transposed row: every 4th starts 16 banks on
+            constexpr int kPart = std::max(32 * 256, 16 * kTRow);
+            static_assert(4 * kPart <= (int)sizeof(smem), "epilogue LDS");
+            __syncthreads();
+            uint8_t *const stg = smem + wave_u * kPart;
+            const int mw = m0 + wm * (BMT / 2), nw = n0 + wn * 64;
+            // [m][n]: 32 rows of 256 bytes at a time, 16-byte unit u of row r at u ^ (r % 16)
+#pragma unroll
+            for (int p = 0; p < AF / 2; ++p) {
+#pragma unroll
+                for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const v4i a4 = acc[i][2 * p + jj];
+                        *reinterpret_cast<v4i *>(stg + (16 * jj + r16) * 256 + 16 * ((4 * i + cq) ^ r16)) =
+                            v4i{a4[0] >> 8, a4[1] >> 8, a4[2] >> 8, a4[3] >> 8};
+                    }
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int r = 4 * q + (lane >> 4), m = mw + 32 * p + r, n = nw + 4 * (lane & 15);
+                    const v4i v = *reinterpret_cast<const v4i *>(stg + r * 256 + 16 * ((lane & 15) ^ (r & 15)));
+                    if (m < M && n < N) *reinterpret_cast<v4i *>(acc_out + (int64_t)m * N + n) = v;
+                }
+            }
+            // [n][m]: 16 rows of kW entries at a time
+            constexpr int kU = kW / 4, kR = 64 / kU;    // 16-byte units a row, rows an instruction
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                for (int j = 0; j < AF; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        *reinterpret_cast<int *>(stg + (4 * cq + e) * kTRow + 4 * (16 * j + r16)) = acc[i][j][e] >> 8;
+#pragma unroll
+                for (int q = 0; q < 16 / kR; ++q) {
+                    const int r = kR * q + lane / kU, n = nw + 16 * i + r, m = mw + 4 * (lane % kU);
+                    const v4i v = *reinterpret_cast<const v4i *>(stg + r * kTRow + 16 * (lane % kU));
+                    if (n < N && m < M) *reinterpret_cast<v4i *>(acc_out + (int64_t)n * N + m) = v;
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int nb = n0 + wn * 64 + 16 * i + 4 * cq;
@@ -692,13 +749,9 @@ __global__ __launch_bounds__(256, BMT == 64 ? 4 : 2) void k_w4a4_gemm_2cu(const 
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e] >> 8;
                     int32_t *dst = acc_out + (int64_t)m * N + nb;
-                    if (nb + 3 < N && (N & 3) == 0) {
-                        *reinterpret_cast<int4 *>(dst) = make_int4(v[0], v[1], v[2], v[3]);
-                    } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (nb + e < N) dst[e] = v[e];
-                    }
+                    for (int e = 0; e < 4; ++e)
+                        if (nb + e < N) dst[e] = v[e];
                     // mirror of the strictly upper entries: 16 lanes write 64
                     // contiguous bytes of row nb + e
 #pragma unroll
@@ -1512,14 +1565,31 @@ hipError_t launch_code_gram(int B, int n, int k, const uint8_t *codes, int32_t *
                             hipStream_t stream) {
     const int kb = k / 2;
     if (n >= 1024) {
-        const int tiles_m = (n + L_BM - 1) / L_BM, tiles_n = (n + L_BN - 1) / L_BN;
-        int upper = 0;                              // tiles with tn >= 2 tm
-        for (int tm = 0; tm < tiles_m; ++tm) upper += std::max(0, tiles_n - 2 * tm);
-        hipLaunchKernelGGL((k_w4a4_gemm_2cu<256, true, true, false, false>), dim3(upper, B),
-                           dim3(256), 0, stream, codes, nullptr, codes, nullptr, n, n, kb, nullptr,
-                           (int64_t)n, G, upper, tiles_n, (int64_t)n * kb, (int64_t)n * kb,
-                           (int64_t)n * n, 0, (int32_t *)nullptr, 0, 1, (uint32_t *)nullptr);
-        return hipGetLastError();
+        const int tiles_n = (n + L_BN - 1) / L_BN;
+        auto upper = [&](auto bm_c) {               // tiles that reach the diagonal or above
+            constexpr int BMT = decltype(bm_c)::value;
+            int c = 0;
+            for (int tm = 0; tm < (n + BMT - 1) / BMT; ++tm) c += std::max(0, tiles_n - gram_first<BMT>(tm));
+            return c;
+        };
+        auto go = [&](auto bm_c) {
+            constexpr int BMT = decltype(bm_c)::value;
+            const int T = upper(bm_c);
+            hipLaunchKernelGGL((k_w4a4_gemm_2cu<BMT, true, true, false, false>), dim3(T, B), dim3(256), 0,
+                               stream, codes, nullptr, codes, nullptr, n, n, kb, nullptr, (int64_t)n, G, T,
+                               tiles_n, (int64_t)n * kb, (int64_t)n * kb, (int64_t)n * n, 0,
+                               (int32_t *)nullptr, 0, 1, (uint32_t *)nullptr);
+            return hipGetLastError();
+        };
+        // The tallest tiles that give every CU one: 1 x 2333 tokens (d = 5120)
+        // are 100 tiles of 256 rows, 190 of 128 and 379 of 64: 52.7, 35.9 and
+        // 31.8 us.  Shorter tiles read their operands more often, so a batch
+        // that fills the CUs keeps the tall ones.
+        using std::integral_constant;
+        const int cus = device_cus();
+        if ((int64_t)upper(integral_constant<int, 256>{}) * B >= cus) return go(integral_constant<int, 256>{});
+        if ((int64_t)upper(integral_constant<int, 128>{}) * B >= cus) return go(integral_constant<int, 128>{});
+        return go(integral_constant<int, 64>{});
     }
     const dim3 grid((n + BN - 1) / BN, (n + BM - 1) / BM);
     for (int b = 0; b < B; ++b) {

@@ -114,6 +114,16 @@ def test_many_close_candidates(N, K):
     check(vis, con, cls, text, K, 5, 3)
 
 
+@pytest.mark.parametrize("B,N", [(1, 1024), (1, 1027), (5, 1412), (5, 1411),
+                                 (13, 1028), (9, 1281)])
+def test_gram_tile_heights(B, N):
+    """Tiles of 64, 128 and 256 rows, by how many there are; rows of whole
+    16-byte units leave through LDS, others straight from the accumulators;
+    whole and partial tiles."""
+    vis, con, cls, text = synth(51 + N, B, N, 64, 2, 1)
+    check(vis, con, cls, text, 96, 30, 20, samples=[0, B - 1])
+
+
 @pytest.mark.parametrize("N,kind", [(1, "equal"), (2880, "equal"), (2880, "outlier"), (2049, "signs"),
                                     (700, "adjacent"), (1300, "extremes")])
 def test_saliency_score_ranges(N, kind):
