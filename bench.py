@@ -730,13 +730,13 @@ def main():
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms, 4),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "int4 (int8 MFMA, int32 acc)", "data": "synthetic",
+        "dtype": "int4 (6-bit float MFMA, exact integer sums; int8 MFMA for smaller products)", "data": "synthetic",
         "config": {"workload": workload_name(cfg),
                    "B": cfg.B, "N": cfg.N, "d": cfg.d, "K": cfg.K, "T": cfg.T, "J": cfg.J,
                    "M": cfg.M, "parallelism": "single GPU"},
         "roofline": {"bound": "mfma", "achieved": round(gemm_tops, 2), "peak": INT8_PEAK_TOPS,
                      "unit": "TOPS", "frac": round(gemm_tops / INT8_PEAK_TOPS, 4),
-                     "traffic": traffic_from_profile(), "kernel": "k_w4a4_gemm_pt",
+                     "traffic": traffic_from_profile(), "kernel": "k_w4a4_gemm_f6 and its operand rewrite k_codes_f6",
                      "per_launch": "2*M*n_out*k_in int ops, averaged over the 4 launches of a step "
                                    "(HIP events around the step's GEMM phase); traffic in HBM "
                                    "bytes per launch"},
