@@ -875,28 +875,33 @@ inline size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct CalibPlan {
     int Mp, nsA, jsA, nsW, jsW, nbA, nloss, tilesMA, tilesNW;
-    int capA, capW;     // splits that the workspace has room for (>= nsA, nsW)
 };
 
+// BLOCK: the plan of a linear inside a block, whose input gradient is an fp32
+// sum over the activation side's splits (k_blk_input_grad) that the next group
+// rounds to bf16.  Another number of splits moves the block's gradients by
+// ~1e-4 relative (5 instead of 6 at 384 tokens of a 7B block), so a block
+// keeps as many as fill the CUs and does not follow the rounds.
+template <bool BLOCK>
 CalibPlan calib_plan(int M, int N, int K) {
     CalibPlan p;
     p.Mp = (M + 63) / 64 * 64;
     const int kt = K / BB;
     p.tilesMA = (M + BB - 1) / BB;
     p.tilesNW = (N + BB - 1) / BB;
-    auto splits = [](int tiles, int J, int &ns, int &js, int &cap) {
+    auto splits = [](int tiles, int J, int &ns, int &js) {
         // Two work-groups fit on each of 256 CUs: up to as many splits as fill
-        // them, at least 4 stages per split, and of those the number with the
-        // shortest rounds of work-groups (stages + 10 for the epilogue; a last
-        // round of at most one work-group per CU takes 0.7 of a full one).
-        // 96 tiles of 192 stages: 5 splits (480 work-groups) 47 us, 6 splits
-        // (576) 62 us; 258 tiles of 64 stages: 2 splits 83 us, 3 splits 92 us.
+        // them, at least 4 stages per split, and of those (a single linear's)
+        // the number with the shortest rounds of work-groups (stages + 10 for
+        // the epilogue; a last round of at most one work-group per CU takes 0.7
+        // of a full one).  96 tiles of 192 stages: 5 splits (480 work-groups)
+        // 47 us, 6 splits (576) 62 us; 258 tiles of 64 stages: 2 splits 83 us,
+        // 3 splits 92 us.
         const int top = std::max(1, std::min((512 + tiles - 1) / tiles, J / (4 * BJ)));
         int64_t best = INT64_MAX;
-        for (int n = 1; n <= top; ++n) {
+        for (int n = BLOCK ? top : 1; n <= top; ++n) {
             const int j = ((J + n - 1) / n + BJ - 1) / BJ * BJ;
-            cap = (J + j - 1) / j;              // grows with n
-            const int64_t wgs = (int64_t)tiles * cap, left = wgs % 512;
+            const int64_t wgs = (int64_t)tiles * ((J + j - 1) / j), left = wgs % 512;
             const int64_t cost = (10 * (wgs / 512) + (left == 0 ? 0 : left <= 256 ? 7 : 10)) * (j / BJ + 10);
             if (cost < best) {
                 best = cost;
@@ -905,8 +910,8 @@ CalibPlan calib_plan(int M, int N, int K) {
         }
         ns = (J + js - 1) / js;
     };
-    splits(p.tilesMA * kt, N, p.nsA, p.jsA, p.capA);
-    splits(p.tilesNW * kt, p.Mp, p.nsW, p.jsW, p.capW);
+    splits(p.tilesMA * kt, N, p.nsA, p.jsA);
+    splits(p.tilesNW * kt, p.Mp, p.nsW, p.jsW);
     p.nbA = (M + kRowsA - 1) / kRowsA;
     p.nloss = (N / 64) * (p.Mp / 64);
     return p;
@@ -953,10 +958,10 @@ size_t calib_carve(const CalibPlan &p, int M, int N, int K, uint8_t *base, Calib
     c.shareA = reinterpret_cast<double *>(take((size_t)M * 8));
     c.shareW = reinterpret_cast<double *>(take((size_t)N * 8));
     c.dclipa_part = reinterpret_cast<double *>(take((size_t)p.nbA * 8));
-    c.rowA = reinterpret_cast<float *>(take((size_t)kt * p.capA * M * 4));
-    c.colA = reinterpret_cast<float *>(take((size_t)p.tilesMA * p.capA * K * 4));
-    c.rowW = reinterpret_cast<float *>(take((size_t)kt * p.capW * N * 4));
-    c.colW = reinterpret_cast<float *>(take((size_t)p.tilesNW * p.capW * K * 4));
+    c.rowA = reinterpret_cast<float *>(take((size_t)kt * p.nsA * M * 4));
+    c.colA = reinterpret_cast<float *>(take((size_t)p.tilesMA * p.nsA * K * 4));
+    c.rowW = reinterpret_cast<float *>(take((size_t)kt * p.nsW * N * 4));
+    c.colW = reinterpret_cast<float *>(take((size_t)p.tilesNW * p.nsW * K * 4));
     if (w) *w = c;
     return off;
 }
@@ -966,7 +971,7 @@ hipError_t calib_typed(int M, int N, int K, const void *x, int64_t ldx, const vo
                        int64_t ldw, const float *target, int64_t ldt, const float *sigma,
                        float clip_a, const float *clip_w, float *loss, float *grad_sigma,
                        float *grad_clip_a, float *grad_clip_w, void *ws, hipStream_t stream) {
-    const CalibPlan p = calib_plan(M, N, K);
+    const CalibPlan p = calib_plan<false>(M, N, K);
     CalibWs c;
     calib_carve(p, M, N, K, static_cast<uint8_t *>(ws), &c);
     hipError_t e;
@@ -1503,11 +1508,11 @@ size_t block_carve(int M, int d, int f, int H, uint8_t *base, BlockWs *w) {
     block_groups(d, f, b.g);
     for (int i = 0; i < 4; ++i) {
         BlockGroup &g = b.g[i];
-        g.p = calib_plan(M, g.N, g.K);
+        g.p = calib_plan<true>(M, g.N, g.K);
         const size_t cb = calib_carve(g.p, M, g.N, g.K, nullptr, nullptr);
         uint8_t *cbase = take(cb);
         calib_carve(g.p, M, g.N, g.K, cbase, &g.c);
-        g.gpart = g.dx ? reinterpret_cast<float *>(take((size_t)g.p.capA * M * g.K * 4)) : nullptr;
+        g.gpart = g.dx ? reinterpret_cast<float *>(take((size_t)g.p.nsA * M * g.K * 4)) : nullptr;
     }
     const size_t Md = (size_t)M * d, Mf = (size_t)M * f, HMM = (size_t)H * M * score_ld(M);
     auto h16 = [&](size_t n) { return reinterpret_cast<uint16_t *>(take(n * 2)); };
@@ -1728,7 +1733,7 @@ hipError_t launch_quant_scaled(p4q_dtype dt, int R, int K, const void *z, int64_
 }
 
 size_t calib_linear_workspace_bytes(int M, int N, int K) {
-    return calib_carve(calib_plan(M, N, K), M, N, K, nullptr, nullptr);
+    return calib_carve(calib_plan<false>(M, N, K), M, N, K, nullptr, nullptr);
 }
 
 hipError_t launch_calib_linear(p4q_dtype dt, int M, int N, int K, const void *x, int64_t ldx,

@@ -27,6 +27,8 @@ the oracle and mag the sum of the magnitudes of a component's terms:
 A planted mistake in any derivative moves most components by O(1) of their
 size (the oracle's pins), so it cannot pass; the measured errors are
 printed."""
+from pathlib import Path
+
 import numpy as np
 import pytest
 import torch
@@ -39,6 +41,7 @@ from gpu_util import Guarded, check_canaries, to_gpu, to_np
 pytestmark = pytest.mark.gpu
 
 GROUPS = oracle.BLOCK_GROUPS
+GOLDEN = Path(__file__).parent / "golden"
 REL, ABS = 2.0 ** -5, 2.0 ** -6
 
 
@@ -149,6 +152,26 @@ def test_block_repeat_is_stable():
     a, b = run(p, t), run(p, t)
     for x, y in zip(a, b):
         assert np.allclose(x, y, rtol=1e-5, atol=1e-6 * np.abs(y).max())
+
+
+def test_block_gradients_keep_their_bits():
+    """The block's gradients pass through fp32 sums over the splits of the
+    backward products, rounded to bf16 by the next group: another grouping
+    moves the weight clip gradients by 5.7e-5 in the 2-norm here.  Pinned to
+    recorded values, within the two units that the order of the float64 sums behind
+    them leaves to an fp32 result."""
+    rec = {}
+    for line in (GOLDEN / "calib_block_gradients.txt").read_text().splitlines():
+        if not line.startswith("#"):
+            name, step, *vals = line.split()
+            rec[name] = int(step), np.array(vals, dtype=np.float32)
+    p = calib_block_problem(17, 67, 2048, 4096, 16)
+    res = dict(zip(("loss", "gs", "gca", "gcw"), run(p, p.x.astype(np.float32))))
+    for name, (step, vals) in rec.items():
+        got = res[name][::step].astype(np.float32)
+        assert got.shape == vals.shape
+        off = np.abs(got.astype(np.float64) - vals) > 2.0 ** -22 * np.abs(vals)
+        assert not off.any(), (name, int(off.sum()), got[off][:3], vals[off][:3])
 
 
 @pytest.mark.slow
