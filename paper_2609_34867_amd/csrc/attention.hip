@@ -35,7 +35,7 @@
 // us; q, k, v and the output take 73 us at the rate of a copy.  Reading Q
 // and writing the output of 128 queries alone (no tiles) takes 42 us, each
 // tile of the two work-groups on a CU 2 us, most of it waiting: two
-// wavefronts per SIMD (206 registers, 64 KB of LDS per work-group) do not
+// wavefronts per SIMD (224 registers, 64 KB of LDS per work-group) do not
 // cover the chain S^T -> maximum -> exp2 -> P V.  Work-groups of two
 // wavefronts: 172 us; neighbouring samples instead of neighbouring query
 // tiles on an XCD: 148 us.
@@ -180,9 +180,12 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attention(const uint16_t *__rest
     // One tile of 64 keys from LDS buffer kt & 1, both 32-key halves at once:
     // their S^T products are two independent MFMA chains, and one softmax
     // update (one max, one rescale decision, one sum) covers the 64 keys.
-    // The next tile's loads are issued on the way.
-    auto tile_keys = [&](int kt) __attribute__((always_inline)) {
-        constexpr int NH = 2;
+    // NH = 1: only the first half has keys at or before this wavefront's last
+    // query (causal diagonal); the second is skipped, since weights of 0 would
+    // still turn a non-finite row of V into NaN.  The next tile's loads are
+    // issued on the way.
+    auto tile_keys = [&](int kt, auto nh_c) __attribute__((always_inline)) {
+        constexpr int NH = decltype(nh_c)::value;
         const uint8_t *sb = smem + (kt & 1) * kTile;
         const int k0 = kt * kKT;
         auto k_read = [&](int hf, int s) __attribute__((always_inline)) {
@@ -295,10 +298,17 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attention(const uint16_t *__rest
     // tile kt has landed from every wavefront, and every wavefront is done
     // with tile kt - 1, whose buffer the loads of tile kt + 1 overwrite
     auto arrive = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory"); };
+    // a wavefront whose queries are the first half of its last tile's keys
+    const bool half = CAUSAL && nlive > 0 && (qw0 & (kKT - 1)) == 0;
     int kt = 0;
-    for (; kt < nlive; ++kt) {
+    for (; kt < nlive - (int)half; ++kt) {
         arrive();
-        tile_keys(kt);
+        tile_keys(kt, std::integral_constant<int, 2>{});
+    }
+    if (half) {
+        arrive();
+        tile_keys(kt, std::integral_constant<int, 1>{});
+        ++kt;
     }
     for (; kt < ntiles; ++kt) {
         arrive();

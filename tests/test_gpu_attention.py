@@ -114,3 +114,21 @@ def test_more_work_groups_than_one_grid_dimension():
     t = torch.randn((B, 3 * HD), generator=g, device="cuda:0", dtype=torch.float16)
     out = p4q.attention_prefill(t[:, :HD], t[:, HD:2 * HD], t[:, 2 * HD:], B, H, True)
     assert torch.equal(out, t[:, 2 * HD:])
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_nonfinite_rows_stay_behind_the_diagonal(dtype):
+    """Rows of V with infinities and NaN reach no query of an earlier group of
+    32 (the wavefront's queries): keys past a wavefront's last query are not
+    multiplied, not even by weights of 0."""
+    B, L, H = 1, 300, 2
+    HD = H * D
+    clean = to_gpu(make_qkv(71, B, L, H, dtype), dtype)
+    ref = p4q.attention_prefill(clean[:, :HD], clean[:, HD:2 * HD], clean[:, 2 * HD:], B, H, True)
+    for row, bad in ((32, float("inf")), (96, float("nan")), (160, -float("inf")), (64, float("inf")), (299, float("nan"))):
+        t = clean.clone()
+        t[row, 2 * HD:] = bad
+        out = p4q.attention_prefill(t[:, :HD], t[:, HD:2 * HD], t[:, 2 * HD:], B, H, True)
+        n = row // 32 * 32
+        assert torch.equal(out[:n], ref[:n]), row
+        assert not torch.isfinite(out[row]).any()
