@@ -88,6 +88,18 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
     else return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{lo, hi}, v2h));
 }
 
+// the same of lo * c and hi * c.  In fp16 the product is rounded once, straight
+// to 16 bits (v_fma_mixlo_f16), which takes a conversion of its own for each: the
+// packed one is handed products that are already rounded to fp32.
+template <bool BF16>
+__device__ __forceinline__ uint32_t pack2_scaled(float lo, float hi, float c) {
+    if constexpr (BF16) return pack2<true>(lo * c, hi * c);
+    else {
+        const _Float16 a = (_Float16)(lo * c), b = (_Float16)(hi * c);
+        return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
+    }
+}
+
 template <int NW, bool BF16, bool CAUSAL>
 __global__ __launch_bounds__(64 * NW, 2) void k_attention(const uint16_t *__restrict__ q,
                                                           const uint16_t *__restrict__ k,
@@ -327,8 +339,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attention(const uint16_t *__rest
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int u = 8 * db + 2 * j + g;
-            const uint2 w = make_uint2(pack2<BF16>(acc[db][4 * j] * inv, acc[db][4 * j + 1] * inv),
-                                       pack2<BF16>(acc[db][4 * j + 2] * inv, acc[db][4 * j + 3] * inv));
+            const uint2 w = make_uint2(pack2_scaled<BF16>(acc[db][4 * j], acc[db][4 * j + 1], inv),
+                                       pack2_scaled<BF16>(acc[db][4 * j + 2], acc[db][4 * j + 3], inv));
             *reinterpret_cast<uint2 *>(stg + c32 * kRow + 8 * (u ^ ((c32 & 15) << 1))) = w;
         }
     const bool vec16 = (ldo & 7) == 0 && (reinterpret_cast<uintptr_t>(o) & 15) == 0;

@@ -132,3 +132,26 @@ def test_nonfinite_rows_stay_behind_the_diagonal(dtype):
         n = row // 32 * 32
         assert torch.equal(out[:n], ref[:n]), row
         assert not torch.isfinite(out[row]).any()
+
+
+def test_fp16_output_is_rounded_once():
+    """Equal scores (q = 0) and integer V: every weight is 1 and the sums are
+    exact, so the output is sum * fl32(1 / L) rounded to fp16 -- once, not to
+    fp32 in between.  The two differ where sum / L is a tie of fp16: the fp32
+    product falls on it, the exact one beside it."""
+    B, L, H = 16, 37, 40
+    HD = H * D
+    g = torch.Generator(device="cuda:0").manual_seed(9)
+
+    def ints(rows, lo, hi):
+        return torch.randint(lo, hi, (B, rows, HD), generator=g, device="cuda:0")
+
+    v = torch.cat([2 * ints(20, 1500, 2048), ints(17, 1000, 2048)], 1)   # exact in fp16
+    t = torch.zeros((B * L, 3 * HD), dtype=torch.float16, device="cuda:0")
+    t[:, 2 * HD:] = v.view(B * L, HD).half()
+    out = to_np(p4q.attention_prefill(t[:, :HD], t[:, HD:2 * HD], t[:, 2 * HD:], B, H, False))
+    sums = v.double().sum(1).cpu().numpy()
+    exact = sums * np.float64(np.float32(1.0) / np.float32(L))      # 17 + 24 bits: exact in float64
+    once = exact.astype(np.float16)
+    assert (exact.astype(np.float32).astype(np.float16) != once).mean() > 1e-3
+    assert np.array_equal(out.reshape(B, L, HD), np.broadcast_to(once[:, None], (B, L, HD)))
