@@ -127,7 +127,10 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attention(const uint16_t *__rest
 
     // DMA of a tile: instruction n of a wavefront fills rows 4 (NI wave + n)
     // + lane / 16 of the operand; slot lane % 16 takes the chunk that k_slot /
-    // v_slot place there (both are their own inverses)
+    // v_slot place there (both are their own inverses).  Offsets have 32 bits:
+    // L ld2 < 2^31, but (with L <= 62 and rows of many MB) not 63 ld2, so rows past
+    // L of the first tile get an offset past any span.  Those of a later tile lie
+    // below 2 L ld2.
     const uint32_t span = (uint32_t)((int64_t)L * ld * 2);
     const v4i dK = buffer_desc(k + base, span), dV = buffer_desc(v + base, span);
     const uint32_t ld2 = (uint32_t)(ld * 2);
@@ -136,8 +139,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attention(const uint16_t *__rest
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
         const int r = drow + 4 * n;
-        vok[n] = (uint32_t)r * ld2 + 16u * (uint32_t)k_slot(r, lane & 15);
-        vov[n] = (uint32_t)r * ld2 + 16u * (uint32_t)v_slot(r, lane & 15);
+        const uint32_t row = r < L ? (uint32_t)r * ld2 : 0x80000000u;
+        vok[n] = row + 16u * (uint32_t)k_slot(r, lane & 15);
+        vov[n] = row + 16u * (uint32_t)v_slot(r, lane & 15);
     }
     const uint32_t lds0 = lds_addr(smem) + (uint32_t)(wave * NI * 1024);
     // (no tile kt: empty descriptors, nothing is read)

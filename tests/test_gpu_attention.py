@@ -155,3 +155,20 @@ def test_fp16_output_is_rounded_once():
     once = exact.astype(np.float16)
     assert (exact.astype(np.float32).astype(np.float16) != once).mean() > 1e-3
     assert np.array_equal(out.reshape(B, L, HD), np.broadcast_to(once[:, None], (B, L, HD)))
+
+
+@pytest.mark.parametrize("L", [1, 17, 62])
+def test_rows_of_many_megabytes(L):
+    """Row strides close to the limit L * ld * 2 < 2^31: the offsets of the
+    tile's rows past L would pass 2^32 and come round to memory that is not
+    the operand's.  Everything between the rows is infinite."""
+    H = 2
+    HD = H * D
+    ld = ((1 << 30) - 1) // L // 8 * 8
+    rows = to_gpu(make_qkv(72 + L, 1, L, H, "fp16"))
+    ref = p4q.attention_prefill(rows[:, :HD], rows[:, HD:2 * HD], rows[:, 2 * HD:], 1, H, True)
+    buf = torch.full(((L - 1) * ld + 3 * HD,), float("inf"), dtype=torch.float16, device=rows.device)
+    wide = buf.as_strided((L, 3 * HD), (ld, 1))
+    wide.copy_(rows)
+    out = p4q.attention_prefill(wide[:, :HD], wide[:, HD:2 * HD], wide[:, 2 * HD:], 1, H, True)
+    assert torch.equal(out, ref)
