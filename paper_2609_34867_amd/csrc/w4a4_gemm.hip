@@ -1314,8 +1314,10 @@ __global__ __launch_bounds__(64 * NW) void k_w4a4_gemv(const uint8_t *__restrict
 }  // namespace
 
 // Dispatch of the prefill shapes (M > 16):
-//  * M >= 1024 and N >= 1024: 256 x 128 tiles, two blocks per CU, persistent
-//    over their tiles (k_w4a4_gemm_pt);
+//  * M >= 1024 and N >= 1024: 256 x 128 int8 tiles, two blocks per CU,
+//    persistent over their tiles (k_w4a4_gemm_pt), or, given the caller's
+//    workspace and a product large enough (use_f6), 256 x 256 tiles on the
+//    6-bit matrix instructions (w4a4_f6.hip);
 //  * M < 1024 and N >= 1024 (one image's pruned sequence): k_w4a4_gemm_2cu
 //    with 128 x 128 tiles, or 64 x 128 (mid_bm); given the caller's
 //    workspace, the tiles past the last whole round per CU are split along
@@ -1328,19 +1330,26 @@ static bool use_mid_tiles(int M, int N) { return M > 16 && M < 1024 && N >= 1024
 // The 6-bit matrix path (w4a4_f6.hip; needs the caller's workspace) against
 // the int8 tiles.  It pays a pass that rewrites both operands (9 us at 4096 +
 // 4096 rows of K = 4096, 22 us at 11264 + 12288) and its 256 x 256 tiles take
-// one CU each, so it needs rows to spread the pass over and tiles for more
-// than half of the CUs.  Measured, int8 / 6-bit us: K = 4096, M x N =
-// 11264 x 22016: 736 / 532, 4096 x 12288: 146 / 121, 1536 x 12288: 80 / 78,
-// 4096 x 4096 (256 tiles): 50 / 47; 1024 x 22016: 82 / 86, 3072 x 4096 (192
-// tiles): 43 / 45, 2048 x 4096 (128 tiles): 35 / 42.  Longer rows hide more
-// of the per-tile cost: K = 11008, 2304 x 4096 (144 tiles): 98 / 82, but
-// 2048 x 4096 (128 tiles) 83 / 82.  The operands' copy is kept under 1 GiB.
+// one CU each, whose epilogue nothing covers, so it needs rows to spread the
+// pass over, tiles for more than half of the CUs, and k to cover the rest.
+// Measured, int8 / 6-bit us:
+//  * K = 4096, M x N = 11264 x 22016: 736 / 532, 4096 x 12288: 146 / 121, 1536 x
+//    12288: 80 / 78, 4096 x 4096 (256 tiles): 50 / 47; 1024 x 22016: 82 / 86,
+//    3072 x 4096 (192 tiles): 43 / 45, 2048 x 4096 (128 tiles): 35 / 42.  K =
+//    11008, 2304 x 4096 (144 tiles): 98 / 82, but 2048 x 4096 (128) 83 / 82.
+//  * Below K = 4096 only many tiles pay.  K = 3072: 512 tiles 82 / 74, 516: 101 /
+//    99; 384: 67 / 67, 288: 64 / 64, 280: 64 / 66, 256: 42 / 44.  K = 2048: 688
+//    tiles 84 / 80, 704: 84 / 80, 768: 86 / 80; 516: 73 / 76, 512: 61 / 61, 384: 47 /
+//    52, 256: 32 / 36.  K = 1024: 2112 tiles 138 / 140, 768: 53 / 59, 256: 22 / 28.
+//    K = 512: 3784 tiles 157 / 167, 256: 15 / 21; K = 128, 2112: 56 / 81, 228: 14 / 26.
+// The operands' copy is kept under 1 GiB.
 constexpr int kF6MinRows = 1536;
+constexpr int kF6MinK = 2048;
 static bool use_f6(int M, int N, int K) {
-    if (!use_large_tiles(M, N) || M < kF6MinRows) return false;
+    if (!use_large_tiles(M, N) || M < kF6MinRows || K < kF6MinK) return false;
     const int64_t T = (((int64_t)M + 255) / 256) * (((int64_t)N + 255) / 256);
-    return (T >= 224 || (T > 128 && K >= 5120)) && T < (1 << 30) &&
-           gemm_f6_bytes(M, N, K) <= ((size_t)1 << 30);
+    const int64_t least = K >= 5120 ? 129 : K >= 4096 ? 224 : (5 << 18) / K;   // 640 at K = 2048, 426 at 3072
+    return T >= least && T < (1 << 30) && gemm_f6_bytes(M, N, K) <= ((size_t)1 << 30);
 }
 
 // Tile height of the mid path: 128 rows, or 64 where 128-row tiles would

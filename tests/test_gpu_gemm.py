@@ -371,13 +371,14 @@ def test_split_k_graph_replays(shape):
     del g
 
 
-@pytest.mark.parametrize("shape,ldy,off", [((1537, 4700, 5152), 4700, 0), ((1800, 7000, 160), 7003, 0),
-                                           ((1536, 9500, 128), 9500, 1), ((2048, 7168, 256), 7168, 0)])
+@pytest.mark.parametrize("shape,ldy,off", [((1537, 4700, 5152), 4700, 0), ((1800, 7000, 4128), 7003, 0),
+                                           ((1536, 27000, 2080), 27000, 1), ((2048, 7168, 4096), 7168, 0)])
 def test_f6_path(shape, ldy, off):
     """The 6-bit matrix path: tiles ragged in M and N, an odd number of
-    128-value stages and a ragged last one (5152), fewer stages than the ring
-    (128, 160, 256), rows and a base that allow no 16-byte stores.  Exact sums:
-    equal to the oracle bit for bit, in both output types."""
+    128-value stages and a ragged last one (2080, 4128, 5152), rows and a base
+    that allow no 16-byte stores, work-groups of several tiles (27000 columns:
+    636 tiles).  Exact sums: equal to the oracle bit for bit, in both output
+    types."""
     M, N, K = shape
     dev = torch.device("cuda:0")
     ws = p4q.w4a4_linear_workspace(M, N, K, dev)
