@@ -118,10 +118,22 @@ __global__ __launch_bounds__(256) void k_codes_f6(const uint8_t *__restrict__ a,
 // acc += w a^T, both operands E3M2.  Inline assembly, so that the 256
 // accumulators stay in the accumulation registers: with the builtin the
 // register allocator moved them through the other half of the register file
-// at every stage (263 spills).  The caller keeps the distance that a read of
-// acc needs after the last one.
+// at every stage (263 spills).  The compiler knows no hazards of it: the
+// caller keeps the distances to the writes before the first and the reads after
+// the last one, and holds the accumulators behind them (hold_acc).
 __device__ __forceinline__ void mfma_f6(v6i w, v6i a, v4f &acc) {
     asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 cbsz:3 blgp:3" : "+a"(acc) : "v"(w), "v"(a));
+}
+
+// No instruction: every use of acc before it stays before, every one after it
+// after, in the order of the other volatile statements.
+template <int NF>
+__device__ __forceinline__ void hold_acc(v4f (&acc)[NF][NF]) {
+    static_assert(NF == 8, "operands");
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+        asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]),
+                     "+a"(acc[i][4]), "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7]));
 }
 
 // 256 x 256 tile on 4 wavefronts of 128 x 128 (one per SIMD: 256 accumulator
@@ -271,6 +283,7 @@ __global__ __launch_bounds__(256, 1) void k_w4a4_gemm_f6(
         for (int i = 0; i < NF; ++i)
 #pragma unroll
             for (int j = 0; j < NF; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        hold_acc(acc);
         asm volatile("s_nop 7" ::: "memory");              // zeroed accumulators before the first MFMA
         for (int kt = 0; kt < KT; kt += 2) {
             stage(acc, std::integral_constant<int, 0>{});
@@ -288,6 +301,7 @@ __global__ __launch_bounds__(256, 1) void k_w4a4_gemm_f6(
         // 16 bytes per lane and stored as whole 256-byte row segments.
         // (the nops: the distance from the last MFMA to the reads of acc)
         asm volatile("s_nop 15\n\ts_nop 15\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        hold_acc(acc);
         int r16 = lane & 15, cq = lane >> 4, lanee = lane;
         asm volatile("" : "+v"(r16), "+v"(cq), "+v"(lanee));
         uint8_t *stg = smem + (rslot == 0 ? kRing - 1 : rslot - 1) * kStageF + wave_u * 8192;
