@@ -1418,7 +1418,8 @@ static size_t mid_split_bytes(const MidPlan &p) {
 }
 
 // Small-M shapes with fewer 128 x 128 tiles than CUs split K across
-// work-groups (exact int32 partials, summed by the epilogue kernel):
+// work-groups (exact int32 partials behind the workspace's arrival counters,
+// summed by the epilogue kernel):
 // S = ceil(256 / tiles), at most 4, each slice at least 4 k-tiles of 256.
 // Not for the decode GEMV or the tile kernels above, nor when N % 4 != 0
 // (the epilogue writes 4 outputs per thread).
@@ -1452,7 +1453,7 @@ size_t gemm_workspace_bytes(int M, int N, int K) {
     if (use_f6(M, N, K)) return kArrivalBytes + gemm_f6_bytes(M, N, K);
     if (use_mid_tiles(M, N)) return mid_split_bytes(mid_plan(M, N, K));
     const int S = small_m_splits(M, N, K);
-    return S > 1 ? (size_t)S * M * N * 4 : 0;
+    return S > 1 ? kArrivalBytes + (size_t)S * M * N * 4 : 0;
 }
 
 hipError_t launch_w4a4_gemm(int M, int N, int K, const uint8_t *a, const float *sa,
@@ -1543,7 +1544,9 @@ hipError_t launch_w4a4_gemm(int M, int N, int K, const uint8_t *a, const float *
     const int S = small_m_splits(M, N, K);
     if (S > 1 && ws_ok) {
         const int kt_all = (K / 2 + KS_ROW - 1) / KS_ROW, kps = (kt_all + S - 1) / S;
-        int32_t *part = static_cast<int32_t *>(ws);
+        // behind the arrival counters, which a workspace shared with a
+        // split tile launch keeps at zero
+        int32_t *part = reinterpret_cast<int32_t *>(static_cast<uint8_t *>(ws) + kArrivalBytes);
         const dim3 gs(grid.x, grid.y, (kt_all + kps - 1) / kps);
         const int Sr = (int)gs.z;
         if (bf16) {

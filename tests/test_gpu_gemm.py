@@ -420,3 +420,21 @@ def test_f6_path_largest_sums():
     _, acc = p4q.w4a4_linear(a, one_a, w, one_w, return_acc=True, workspace=ws)
     _, ref = p4q.w4a4_linear(a, one_a, w, one_w, return_acc=True, workspace=none)
     assert torch.equal(acc, ref)
+
+
+def test_workspace_shared_by_narrow_and_tile_splits():
+    """One workspace for launches of both kinds of K split: the narrow one
+    (N < 1024, slices summed by a second kernel) leaves the head of the
+    workspace zero for the tile one, which counts arrivals there."""
+    dev = torch.device("cuda:0")
+    narrow, tiles = (96, 512, 4096), (384, 4096, 4096)
+    sizes = [p4q.lib().p4q_w4a4_linear_workspace_bytes(*s) for s in (narrow, tiles)]
+    assert min(sizes) > 4096
+    ws = torch.zeros(max(sizes), dtype=torch.uint8, device=dev)
+    for M, N, K in (narrow, tiles, narrow):
+        ap, sa, wp, sw = codes_for(M, N, K, seed=M + N)
+        racc, ry = oracle.w4a4_linear(ap, sa, wp, sw, "bf16")
+        y, acc = run_gpu(ap, sa, wp, sw, "bf16", workspace=ws)
+        assert (m := first_mismatch(acc, racc.astype(np.int32))) is None, m
+        assert (m := first_mismatch(bits(y), bits(ry))) is None, m
+        assert int(ws[:4096].count_nonzero()) == 0, (M, N, K)
