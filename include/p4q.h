@@ -384,8 +384,9 @@ int p4q_calib_block_grad(p4q_dtype dt, int M, int d, int f, int H, const void *x
  *     these integers are exact.
  *   With ws NULL, smaller or misaligned the call runs without it.  The
  *   results are identical either way (integer sums).  The first 4096 bytes
- *   hold per-tile arrival counters: they must be zero before the first call
- *   that uses the workspace, and every call leaves them zero; the rest need
+ *   hold per-tile arrival counters, which calls with M < 1024 read and no
+ *   other does: they must be zero before the first such call that uses the
+ *   workspace, and every call leaves them as it met them (zero); the rest need
  *   not be cleared.  Calls that share a workspace must not overlap.  The
  *   size depends on the current device (its number of compute units): query
  *   it with that device current.

@@ -450,6 +450,22 @@ def w4a4_linear_workspace(M: int, N_out: int, K_in: int, device) -> Optional[tor
     return ws
 
 
+def _own_linear_workspace(M: int, N_out: int, K_in: int, device) -> Optional[torch.Tensor]:
+    """Workspace of one call that was given none: the arrival counters are
+    cleared only where the call counts (M < 1024), and a device without room
+    for it (up to 1 GiB for large products) runs the call without."""
+    n = lib().p4q_w4a4_linear_workspace_bytes(M, N_out, K_in)
+    if n == 0:
+        return None
+    try:
+        ws = torch.empty(n, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+    if M < 1024:
+        ws[:4096].zero_()
+    return ws
+
+
 def w4a4_linear(a_codes: torch.Tensor, a_scales: torch.Tensor, w_codes: torch.Tensor,
                 w_scales: torch.Tensor, out_dtype: torch.dtype = torch.bfloat16,
                 y: Optional[torch.Tensor] = None, acc_out: Optional[torch.Tensor] = None,
@@ -457,9 +473,9 @@ def w4a4_linear(a_codes: torch.Tensor, a_scales: torch.Tensor, w_codes: torch.Te
     """W4A4 linear (p4q_w4a4_linear): a_codes [M, K_in/2], w_codes [N_out, K_in/2]
     -> y [M, N_out] (out_dtype); also the int32 accumulators when return_acc.
     Without `workspace` one of the size the library asks for is allocated
-    (small M splits K across work-groups with it, large products take the
-    6-bit matrix path); a smaller one, e.g. empty, runs without it.  Results
-    are identical either way."""
+    if there is room (small M splits K across work-groups with it, large
+    products take the 6-bit matrix path); a smaller one, e.g. empty, runs
+    without it.  Results are identical either way."""
     if a_codes.dim() != 2 or w_codes.dim() != 2:
         raise ValueError("a_codes and w_codes must be 2-D [rows, K_in/2]")
     M, kb = a_codes.shape
@@ -482,7 +498,7 @@ def w4a4_linear(a_codes: torch.Tensor, a_scales: torch.Tensor, w_codes: torch.Te
     if return_acc and acc_out is None:
         acc_out = torch.empty((M, N_out), dtype=torch.int32, device=dev)
     if workspace is None:
-        workspace = w4a4_linear_workspace(M, N_out, K_in, dev)
+        workspace = _own_linear_workspace(M, N_out, K_in, dev)
     ws_bytes = 0 if workspace is None else workspace.numel()
     st = lib().p4q_w4a4_linear(M, N_out, K_in, _ptr(a_codes), _ptr(a_scales), _ptr(w_codes),
                                _ptr(w_scales), _dtype_code(y.dtype), _ptr(y), y.stride(0),

@@ -438,3 +438,24 @@ def test_workspace_shared_by_narrow_and_tile_splits():
         assert (m := first_mismatch(acc, racc.astype(np.int32))) is None, m
         assert (m := first_mismatch(bits(y), bits(ry))) is None, m
         assert int(ws[:4096].count_nonzero()) == 0, (M, N, K)
+
+
+def test_no_room_for_the_default_workspace(monkeypatch):
+    """A large product called without a workspace runs where the allocator has
+    no room for one (as it does with an empty one), with the same result."""
+    M, N, K = 4096, 4096, 4096
+    dev = torch.device("cuda:0")
+    need = p4q.lib().p4q_w4a4_linear_workspace_bytes(M, N, K)
+    ops = [to_gpu(t) for t in codes_for(M, N, K, 21)]
+    ref = p4q.w4a4_linear(*ops, workspace=torch.empty(0, dtype=torch.uint8, device=dev))
+    empty, refused = torch.empty, []
+
+    def no_room(*size, **kw):
+        if size == (need,):
+            refused.append(need)
+            raise torch.OutOfMemoryError("no room")
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", no_room)
+    y = p4q.w4a4_linear(*ops)
+    assert refused and torch.equal(y.view(torch.int16), ref.view(torch.int16))
