@@ -158,7 +158,9 @@ def test_block_gradients_keep_their_bits():
     """The block's gradients pass through fp32 sums over the splits of the
     backward products, rounded to bf16 by the next group: another grouping
     moves the weight clip gradients by 5.7e-5 in the 2-norm here.  Pinned to
-    recorded values, within the two units that the order of the float64 sums behind
+    recorded values (taken with the attention products as chains of fused
+    multiply-adds over ascending k, which the fp32 matrix instructions repeat
+    bit for bit), within the two units that the order of the float64 sums behind
     them leaves to an fp32 result."""
     rec = {}
     for line in (GOLDEN / "calib_block_gradients.txt").read_text().splitlines():

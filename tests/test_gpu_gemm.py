@@ -398,12 +398,47 @@ def test_f6_path(shape, ldy, off):
                 assert (m := first_mismatch(to_np(acc), racc.astype(np.int32))) is None, (name, m)
             assert (m := first_mismatch(bits(to_np(y.contiguous())), bits(ry))) is None, (name, with_acc, m)
             assert bool((buf[:2 * off] == 7).all()) and bool((buf[2 * off + M * ldy:] == 7).all())
+            assert bool((buf[2 * off:2 * off + M * ldy].view(M, ldy)[:, N:] == 7).all())
     assert int(ws[:4096].count_nonzero()) == 0
 
 
+@pytest.mark.parametrize("shape", [(4000, 12200, 4096), (4000, 12200, 128), (1300, 22100, 160)])
+def test_several_tiles_per_work_group(shape):
+    """Persistent work-groups that walk more than one tile, ragged in M and N:
+    768 tiles of 256 x 256 on the 6-bit path and 1536 of 256 x 128 on the int8
+    path (with two work-groups per CU), which the same call takes without the
+    workspace; shapes that only the int8 path takes, with fewer k-tiles than
+    its ring.  Whole outputs of the two paths are equal, and the oracle's at
+    the first and last rows and at sampled entries; the int8-only shapes are
+    compared in full."""
+    M, N, K = shape
+    dev = torch.device("cuda:0")
+    ap, sa, wp, sw = codes_for(M, N, K, seed=M + N + K)
+    ops = [to_gpu(t) for t in (ap, sa, wp, sw)]
+    ws = p4q.w4a4_linear_workspace(M, N, K, dev)
+    assert (ws is not None) == (K >= 2048)
+    none = torch.empty(0, dtype=torch.uint8, device=dev)
+    rng = np.random.default_rng(K)
+    for dt in (torch.bfloat16, torch.float16):
+        y8, acc8 = p4q.w4a4_linear(*ops, dt, return_acc=True, workspace=none)
+        assert torch.equal(p4q.w4a4_linear(*ops, dt, workspace=none).view(torch.int16), y8.view(torch.int16))
+        if ws is None:
+            racc, ry = oracle.w4a4_linear(ap, sa, wp, sw, "bf16" if dt == torch.bfloat16 else "fp16")
+            assert (m := first_mismatch(to_np(acc8), racc.astype(np.int32))) is None, m
+            assert (m := first_mismatch(bits(to_np(y8)), bits(ry))) is None, m
+            continue
+        y6, acc6 = p4q.w4a4_linear(*ops, dt, return_acc=True, workspace=ws)
+        assert torch.equal(acc6, acc8) and torch.equal(y6.view(torch.int16), y8.view(torch.int16))
+        y6 = p4q.w4a4_linear(*ops, dt, workspace=ws)
+        assert torch.equal(y6.view(torch.int16), y8.view(torch.int16))
+        if dt == torch.bfloat16:
+            check_sampled(ap, sa, wp, sw, to_np(y8), to_np(acc8), rng, edge_rows=16, entries=512)
+
+
 def test_f6_path_largest_sums():
-    """|acc| = 64 K = 2^23 at the largest K_in (all codes -8), and random
-    codes there against the int8 path: fp32 accumulation stays exact."""
+    """|acc| = 64 K = 2^23 at the largest K_in (all codes -8), sums of single
+    units close to it (one product of 49 among 64s: odd), and random codes
+    there against the int8 path: fp32 accumulation stays exact."""
     M, N, K = 1536, 6144, 131072
     dev = torch.device("cuda:0")
     one_a, one_w = torch.ones(M, device=dev), torch.ones(N, device=dev)
@@ -413,6 +448,14 @@ def test_f6_path_largest_sums():
     w = torch.full((N, K // 2), 0x88, dtype=torch.uint8, device=dev)
     _, acc = p4q.w4a4_linear(a, one_a, w, one_w, return_acc=True, workspace=ws)
     assert bool((acc == 64 * K).all())
+    # code 7 at one of four places of each row: 64 (K - 1) + 49 where the two
+    # rows' places meet, 64 (K - 2) - 2 * 56 elsewhere
+    places = torch.tensor([0, 77, 65535, K - 1], device=dev)
+    pm, pn = (places[torch.arange(r, device=dev) * 3 % 4] for r in (M, N))
+    for t, p in ((a, pm), (w, pn)):
+        t[torch.arange(t.shape[0], device=dev), p // 2] = torch.where(p % 2 == 0, 0x87, 0x78).to(torch.uint8)
+    _, acc = p4q.w4a4_linear(a, one_a, w, one_w, return_acc=True, workspace=ws)
+    assert torch.equal(acc, torch.where(pm[:, None] == pn[None, :], 64 * K - 15, 64 * K - 240).int())
     g = torch.Generator(device=dev).manual_seed(5)
     a.random_(0, 256, generator=g)
     w.random_(0, 256, generator=g)
