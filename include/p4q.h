@@ -290,9 +290,9 @@ int p4q_quant_scaled(p4q_dtype dt, int R, int K, const void *z, int64_t ldz,
  * Limits: M >= 1, N % 64 == 0, K % 128 == 0, K <= 16384, M N and N K
  *   < 2^31; ldx, ldw >= K and multiples of 8; ldt >= N, multiple of 4;
  *   clip_a in (0, 1]; x, w, target, sigma 16-byte aligned.
- * The scatter of the row maxima's shares uses float64 atomics: results can
- *   differ between runs in the last bits of float64 sums, far below the
- *   fp32 outputs' precision.
+ * The row maxima's shares are added to their columns with float64 atomics:
+ *   results can differ between runs in the last bits of float64 sums, far
+ *   below the fp32 outputs' precision.
  * ---------------------------------------------------------------------- */
 size_t p4q_calib_linear_workspace_bytes(int M, int N, int K);
 

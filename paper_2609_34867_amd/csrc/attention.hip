@@ -3,7 +3,7 @@
 // key and value caches kept in FP16):
 //     O[t, h] = sum_j softmax_j(<q_t, k_j> / sqrt(D)) v_j,  j <= t when causal.
 //
-// One work-group of NW wavefronts per (32 NW queries, head, sample); each
+// One work-group of 4 wavefronts per (128 queries, head, sample); each
 // wavefront owns 32 queries and walks the key tiles of 64 keys:
 //  * S^T = K Q^T on v_mfma_f32_32x32x16 (K from LDS, Q^T held in registers):
 //    lane l ends up with query l%32 and 16 keys of each 32-key half, so the
@@ -60,7 +60,9 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4s *lds_v4s_t;
 
 constexpr int kD = 128;                 // head dimension
+constexpr int kNW = 4;                  // wavefronts per work-group
 constexpr int kQW = 32;                 // queries per wavefront
+constexpr int kQB = kNW * kQW;          // queries per work-group
 constexpr int kKT = 64;                 // keys per tile
 constexpr int kRow = kD * 2;            // bytes of a K or V row
 constexpr int kOperand = kKT * kRow;    // 16 KB
@@ -100,26 +102,25 @@ __device__ __forceinline__ uint32_t pack2_scaled(float lo, float hi, float c) {
     }
 }
 
-template <int NW, bool BF16, bool CAUSAL>
-__global__ __launch_bounds__(64 * NW, 2) void k_attention(const uint16_t *__restrict__ q,
+template <bool BF16, bool CAUSAL>
+__global__ __launch_bounds__(64 * kNW, 2) void k_attention(const uint16_t *__restrict__ q,
                                                           const uint16_t *__restrict__ k,
                                                           const uint16_t *__restrict__ v, int64_t ld,
                                                           int L, int H, uint16_t *__restrict__ o,
                                                           int64_t ldo, float c2, int total) {
-    constexpr int QB = NW * kQW;            // queries per work-group
-    constexpr int NI = 16 / NW;             // 1 KB DMA instructions per operand and wavefront
+    constexpr int NI = 16 / kNW;            // 1 KB DMA instructions per operand and wavefront
     __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * kTile];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 5, c32 = lane & 31;
-    const int nqt = (L + QB - 1) / QB;
+    const int nqt = (L + kQB - 1) / kQB;
     const int wg = (int)(blockIdx.y * gridDim.x + blockIdx.x);
     if (wg >= total) return;
     const int logical = xcd_logical(wg, total);
     const int bh = logical / nqt, qi = logical - bh * nqt;
     const int qt = CAUSAL ? nqt - 1 - qi : qi;             // longest (causal) first
     const int b = bh / H, h = bh - b * H;
-    const int q0 = qt * QB;
+    const int q0 = qt * kQB;
     const int64_t base = (int64_t)b * L * ld + (int64_t)h * kD;
 
     const int qw0 = q0 + kQW * wave;                       // first query of the wavefront
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attention(const uint16_t *__rest
     }
     const uint32_t lds0 = lds_addr(smem) + (uint32_t)(wave * NI * 1024);
     // (no tile kt: empty descriptors, nothing is read)
-    const int kend = CAUSAL ? min(L, q0 + QB) : L;
+    const int kend = CAUSAL ? min(L, q0 + kQB) : L;
     const int ntiles = (kend + kKT - 1) / kKT;
     auto issue = [&](bool isv, int kt, int n0, int n1) __attribute__((always_inline)) {
         v4i d = isv ? dV : dK;
@@ -374,18 +375,18 @@ hipError_t launch_attention(p4q_dtype dt, int B, int L, int H, const void *q, co
     const uint16_t *qq = static_cast<const uint16_t *>(q), *kk = static_cast<const uint16_t *>(k),
                    *vv = static_cast<const uint16_t *>(v);
     uint16_t *oo = static_cast<uint16_t *>(o);
-    auto go = [&](auto kern, int nw) {
+    auto go = [&](auto kern) {
         // a launch dimension holds fewer than 2^32 threads: many very short
         // samples wrap into the second one
-        const int64_t total = (int64_t)B * H * ((L + 32 * nw - 1) / (32 * nw)), wrap = 1 << 20;
+        const int64_t total = (int64_t)B * H * ((L + kQB - 1) / kQB), wrap = 1 << 20;
         if (total > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
         const dim3 grid((unsigned)std::min(total, wrap), (unsigned)((total + wrap - 1) / wrap));
-        hipLaunchKernelGGL(kern, grid, dim3(64 * nw), 0, stream, qq, kk, vv, ld, L, H, oo, ldo, c2,
+        hipLaunchKernelGGL(kern, grid, dim3(64 * kNW), 0, stream, qq, kk, vv, ld, L, H, oo, ldo, c2,
                            (int)total);
         return hipGetLastError();
     };
-    if (dt == P4Q_BF16) return causal ? go(k_attention<4, true, true>, 4) : go(k_attention<4, true, false>, 4);
-    return causal ? go(k_attention<4, false, true>, 4) : go(k_attention<4, false, false>, 4);
+    if (dt == P4Q_BF16) return causal ? go(k_attention<true, true>) : go(k_attention<true, false>);
+    return causal ? go(k_attention<false, true>) : go(k_attention<false, false>);
 }
 
 }  // namespace p4q

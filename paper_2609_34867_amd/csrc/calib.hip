@@ -27,15 +27,17 @@
 //      linear in g, so the contraction is split freely across work-groups,
 //      each writing its own partial slot.
 //   6. k_calib_rows: per row g_s (deterministic sum of the slots), the clip
-//      gradients, and the row maximum's share g_s clip absmax / 7, added to
-//      its column with float64 atomics.
-//   7. k_calib_cols: with colX / colW the per-column totals of both sides,
+//      gradients, and the row maximum's share g_s clip absmax / 7.
+//   7. k_calib_cols: the shares of the rows whose maximum lies in a column
+//      added to it (float64 atomics in LDS); with colX / colW the per-column totals of both sides,
 //      d sigma_k = (2 / (M N)) (colW_k - colX_k) / sigma_k (the product
 //      X W^T is unchanged when sigma divides one side and multiplies the
 //      other); the loss and the activation clip gradient.
 // The factor 2 / (M N) of the mean squared error is applied once, at the end.
+#include "gemm_device.h"
 #include "p4q_internal.h"
 #include "q4_device.h"
+#include "wave_ops.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -43,7 +45,6 @@
 namespace p4q {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
@@ -428,38 +429,9 @@ constexpr int kOffB = kOffC + BB * kCStride;
 constexpr int kOffS = kOffB + BB * kBStride;
 static_assert(kOffS + 10 * BB * 4 <= 2 * kStage, "epilogue LDS");
 
-__device__ __forceinline__ v4i buffer_rsrc(const void *base, uint32_t bytes) {
-    const uint64_t b = reinterpret_cast<uint64_t>(base);
-    return v4i{(int)(uint32_t)b, (int)((b >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
-}
-
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void lds_dma16(v4i desc, uint32_t voffset, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %2\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-                 :
-                 : "v"(voffset), "s"(desc), "s"(lds)
-                 : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
 __device__ __forceinline__ v16f mfma_bf16(uint4 a, uint4 b, v16f c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a),
                                                    __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
-}
-
-// x of lane ^ m, m < 16, by DPP (4: mirrored halves of 8, mirrored quads)
-template <int m>
-__device__ __forceinline__ float lane_xor(float x) {
-    int v = __builtin_bit_cast(int, x);
-    if constexpr (m == 8) v = __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);       // row_ror:8
-    if constexpr (m == 4) {
-        v = __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true);                         // row_half_mirror
-        v = __builtin_amdgcn_update_dpp(0, v, 0x1B, 0xF, 0xF, true);                          // quad_perm 3,2,1,0
-    }
-    if constexpr (m == 2) v = __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);        // quad_perm 2,3,0,1
-    if constexpr (m == 1) v = __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);        // quad_perm 1,0,3,2
-    return __builtin_bit_cast(float, v);
 }
 
 // Epilogue per element (g = the contraction's value at (i, k), z' the
@@ -483,8 +455,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_calib_bwd(
     const int jb = split * js;
     const int nst = max(0, min(J - jb, js)) / BJ;
 
-    const v4i dP = buffer_rsrc(P + (int64_t)i0 * ldp, (uint32_t)(min(I - i0, BB) * ldp * 2));
-    const v4i dC = buffer_rsrc(C + (int64_t)k0 * ldc, (uint32_t)(BB * ldc * 2));
+    const v4i dP = buffer_desc(P + (int64_t)i0 * ldp, (uint32_t)(min(I - i0, BB) * ldp * 2));
+    const v4i dC = buffer_desc(C + (int64_t)k0 * ldc, (uint32_t)(BB * ldc * 2));
     // DMA: one 1 KB instruction fills 8 LDS rows; lane L -> row +L/8, slot
     // L%8, which holds chunk (L%8) ^ ((row >> 1) & 7).  Wave w copies rows
     // [32w, 32w + 32) of both operands.
@@ -502,8 +474,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_calib_bwd(
         const uint32_t jo = (uint32_t)(jb + st * BJ) * 2u;
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
-            lds_dma16(dP, voP[n] + jo, lds0 + slot * kStage + n * 1024);
-            lds_dma16(dC, voC[n] + jo, lds0 + slot * kStage + kHalfStage + n * 1024);
+            dma16(dP, voP[n] + jo, lds0 + slot * kStage + n * 1024);
+            dma16(dC, voC[n] + jo, lds0 + slot * kStage + kHalfStage + n * 1024);
         }
     };
 
@@ -690,7 +662,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_calib_bwd(
             asm volatile("" : "+v"(lo), "+v"(hi));
             const float send = up ? lo : hi;
             const float keep = up ? hi : lo;
-            colv[v] = keep + lane_xor<m>(send);
+            colv[v] = keep + __uint_as_float(lane_xor<m>(__float_as_uint(send)));
         }
     };
     halve(std::integral_constant<int, 8>{});
@@ -1386,7 +1358,7 @@ __global__ __launch_bounds__(kThreads) void k_blk_out(const uint16_t *__restrict
 // The bf16 contraction operands of a linear group's backward pass from its
 // upstream gradient G [M][N] (fp32): P1 = bf16(G sW[n]) [M][N], P2^T =
 // bf16(G sA[m]) [N][Mp] (rows m >= M zero).  64 x 64 tiles, grid (N / 64,
-// Mp / 64); the grid also clears the float64 scatter targets.
+// Mp / 64).
 __global__ __launch_bounds__(kThreads) void k_blk_upstream(
     const float *__restrict__ G, int64_t ldg, const float *__restrict__ sa,
     const float *__restrict__ sw, int M, int N, int Mp, uint16_t *__restrict__ P1,

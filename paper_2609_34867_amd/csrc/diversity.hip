@@ -161,27 +161,6 @@ __device__ __forceinline__ void wave_min2(uint64_t &k1, uint64_t &k2) {
 }
 
 template <int CTRL>
-__device__ __forceinline__ uint64_t min_dpp(uint64_t a) {
-    const uint64_t b = dpp64<CTRL>(a);
-    return b < a ? b : a;
-}
-
-// smallest key of the wavefront, wave-uniform
-__device__ __forceinline__ uint64_t wave_min1(uint64_t a) {
-    a = min_dpp<0xB1>(a);
-    a = min_dpp<0x4E>(a);
-    a = min_dpp<0x141>(a);
-    a = min_dpp<0x140>(a);
-    uint64_t r = readlane64(a, 0);
-#pragma unroll
-    for (int w = 1; w < 4; ++w) {
-        const uint64_t x = readlane64(a, 16 * w);
-        r = x < r ? x : r;
-    }
-    return r;
-}
-
-template <int CTRL>
 __device__ __forceinline__ uint32_t min_dpp32(uint32_t a) {
     return min(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, CTRL, 0xF, 0xF, false));
 }
@@ -209,15 +188,8 @@ __device__ __forceinline__ void pair_sorted(uint32_t x, uint32_t &lo, uint32_t &
         const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
         a = p[0];
         c = p[1];
-    } else if constexpr (M == 8) {
-        c = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xF, 0xF, false);     // row_ror:8
-    } else if constexpr (M == 4) {
-        c = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xF, 0xF, false);     // row_half_mirror
-        c = (uint32_t)__builtin_amdgcn_mov_dpp((int)c, 0x1B, 0xF, 0xF, false);      // quad_perm 3,2,1,0
-    } else if constexpr (M == 2) {
-        c = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, false);      // quad_perm 2,3,0,1
     } else {
-        c = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, false);      // quad_perm 1,0,3,2
+        c = lane_xor<M>(x);
     }
     lo = min(a, c);
     hi = max(a, c);

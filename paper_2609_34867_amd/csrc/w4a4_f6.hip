@@ -296,7 +296,7 @@ __global__ __launch_bounds__(256, 1) void k_w4a4_gemm_f6(
         const float *s_sw = s_sa + F_BM;
         // Epilogue: each wavefront stages 32 rows x 128 columns at a time in
         // its own 8 KB of the slot whose stage every wave now holds in
-        // registers (stage g + 2's; its next DMA follows the next barrier):
+        // registers (the next tile's first; its next DMA follows the next barrier):
         // 8-byte units, unit block i of row r at i ^ (r % 8), read back as
         // 16 bytes per lane and stored as whole 256-byte row segments.
         // (the nops: the distance from the last MFMA to the reads of acc)
