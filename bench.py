@@ -20,8 +20,10 @@ three events only (after the selector, the quantize calls and the GEMMs), from
 which the per-phase mean, median, p10 and p90 are reported.
 
 Prints ONE JSON line.  value = W4A4 linear ops of the step / step time (TOPS);
-roofline = the GEMM phase against the int8 MFMA peak (published, and measured
-by a microbenchmark of this device); the selector's token rate and HBM
+roofline = the GEMM phase against the peak of the matrix instructions that its
+launches take (6-bit float or int8; published, and for int8 measured by a
+microbenchmark of this device), with its ratio to the int8 peak beside it; the
+selector's token rate and HBM
 fraction beside it.  Also reported, outside the timed steps: the same step at
 batch 1 (LLaVA-NeXT-7B, K = 320 / 640) and at the 13B stress shape, the hot-
 cache GEMM rate, the fused RMSNorm + quantize prologue, the attention prefill,
@@ -43,6 +45,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 INT8_PEAK_TOPS = 5000.0      # MI355X dense int8 MFMA
+F6_PEAK_TOPS = 10000.0       # MI355X dense 6-bit float MFMA
 FP16_PEAK_TFLOPS = 2500.0    # MI355X dense fp16 MFMA
 FP32_PEAK_TFLOPS = 157.3     # MI355X dense fp32
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E
@@ -243,21 +246,41 @@ def gemm_hot(cfg, st, reps=10):
     return e0.elapsed_time(e1) / reps
 
 
+def gemm_peak(cfg):
+    """(peak TOPS, 6-bit launches, launches) of a step's GEMM phase: the
+    launches' operations over the time they take at the peak of the matrix
+    instructions that each runs on.  M >= 1024 asks for a workspace exactly
+    where it takes the 6-bit path."""
+    import paper_2609_34867_amd as p4q
+
+    by_name = {lin.name: lin for lin in cfg.linears}
+    ops = floor = six = n = 0
+    for _, members, _ in launch_groups(cfg):
+        n_out, k_in = sum(by_name[m].n_out for m in members), by_name[members[0]].k_in
+        f6 = cfg.M >= 1024 and p4q.lib().p4q_w4a4_linear_workspace_bytes(cfg.M, n_out, k_in) > 0
+        o = 2 * cfg.M * n_out * k_in
+        ops, six, n = ops + o, six + f6, n + 1
+        floor += o / (F6_PEAK_TOPS if f6 else INT8_PEAK_TOPS)
+    return ops / floor, six, n
+
+
 def config_result(cfg, ms, phases, peak_meas=None):
     """Per-configuration figures of the timed steps."""
     ops = cfg.linear_ops()
+    peak, six, _ = gemm_peak(cfg)
     g, s = dist(phases["gemm"]), dist(phases["select"])
     tops = ops / (g["mean"] * 1e-3) / 1e12
     sel_gbs = selector_bytes(cfg) / (s["mean"] * 1e-3) / 1e9
     out = {"workload": workload_name(cfg), "ms_per_step": round(ms, 4),
            "gemm_tops": round(tops, 2), "gemm_frac_int8_peak": round(tops / INT8_PEAK_TOPS, 4),
-           "gemm_floor_ms": round(ops / (INT8_PEAK_TOPS * 1e12) * 1e3, 4),
+           "gemm_peak_tops": round(peak, 1), "gemm_frac_peak": round(tops / peak, 4),
+           "gemm_floor_ms": round(ops / (peak * 1e12) * 1e3, 4),
            "selector_us": round(s["mean"] * 1e3, 2),
            "selector_tokens_per_s": round(cfg.B * cfg.N / (s["mean"] * 1e-3), 1),
            "selector_gbs": round(sel_gbs, 1), "selector_hbm_frac": round(sel_gbs / HBM_PEAK_GBS, 4),
            "selector_floor_us": round(selector_bytes(cfg) / (HBM_PEAK_GBS * 1e9) * 1e6, 2),
            "phase_ms": {k: dist(v) for k, v in phases.items()}}
-    if peak_meas:
+    if peak_meas and not six:          # the measured ceiling is the int8 instructions'
         out["gemm_frac_measured_mfma_peak"] = round(tops / peak_meas, 4)
     return out
 
@@ -675,15 +698,16 @@ def copy_calibration(dev, nbytes=1 << 30, reps=5):
 
 def traffic_from_profile():
     """HBM bytes per GEMM launch from the committed counter summary, or None
-    when the GEMM source changed after the counters were taken."""
+    when the GEMM sources changed after the counters were taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "hbm_traffic_w4a4_gemm_llava_next_b16.md")
-    src = os.path.join(ROOT, "paper_2609_34867_amd", "csrc", "w4a4_gemm.hip")
+    src = [os.path.join(ROOT, "paper_2609_34867_amd", "csrc", f)
+           for f in ("w4a4_gemm.hip", "w4a4_f6.hip", "gemm_device.h")]
     try:
         fields = dict(l.strip("- \n").split(": ", 1) for l in open(path)
                       if l.startswith("- ") and ": " in l)
-        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
-        if fields.get("w4a4_gemm.hip sha256") != sha:
+        sha = hashlib.sha256(b"".join(open(f, "rb").read() for f in src)).hexdigest()
+        if fields.get("w4a4_gemm.hip + w4a4_f6.hip + gemm_device.h sha256") != sha:
             return None
         return int(fields["hbm bytes per launch"])
     except (OSError, KeyError, ValueError):
@@ -723,6 +747,10 @@ def main():
     ops = cfg.linear_ops()
     gemm_ms = main_cfg["phase_ms"]["gemm"]["mean"]
     gemm_tops = main_cfg["gemm_tops"]
+    peak, six, launches = gemm_peak(cfg)
+    kernel = ("k_w4a4_gemm_f6 and its operand rewrite k_codes_f6" if six == launches else
+              f"int8 tile kernels ({launches - six} launches)"
+              + (f", k_w4a4_gemm_f6 ({six})" if six else ""))
     res = {
         "metric": "W4A4 GEMM TOPS (% int8 MFMA peak) + selector tokens/s, LLaVA-NeXT-7B shape",
         "value": round(ops / (ms * 1e-3) / 1e12, 3),
@@ -734,9 +762,11 @@ def main():
         "config": {"workload": workload_name(cfg),
                    "B": cfg.B, "N": cfg.N, "d": cfg.d, "K": cfg.K, "T": cfg.T, "J": cfg.J,
                    "M": cfg.M, "parallelism": "single GPU"},
-        "roofline": {"bound": "mfma", "achieved": round(gemm_tops, 2), "peak": INT8_PEAK_TOPS,
-                     "unit": "TOPS", "frac": round(gemm_tops / INT8_PEAK_TOPS, 4),
-                     "traffic": traffic_from_profile(), "kernel": "k_w4a4_gemm_f6 and its operand rewrite k_codes_f6",
+        "roofline": {"bound": "mfma", "achieved": round(gemm_tops, 2), "peak": round(peak, 1),
+                     "unit": "TOPS", "frac": round(gemm_tops / peak, 4),
+                     "frac_int8_peak": round(gemm_tops / INT8_PEAK_TOPS, 4),
+                     "traffic": traffic_from_profile() if args.config == "next7b_b16" else None,
+                     "kernel": kernel,
                      "per_launch": "2*M*n_out*k_in int ops, averaged over the 4 launches of a step "
                                    "(HIP events around the step's GEMM phase); traffic in HBM "
                                    "bytes per launch"},
@@ -749,8 +779,11 @@ def main():
     }
     if pk:
         res["measured_peaks"] = pk
-        res["roofline"]["peak_measured"] = pk["mfma_i8_tops"]
-        res["roofline"]["frac_measured"] = round(gemm_tops / pk["mfma_i8_tops"], 4)
+        if six:                            # the measured ceiling is the int8 instructions'
+            res["roofline"]["int8_peak_measured"] = pk["mfma_i8_tops"]
+        else:
+            res["roofline"]["peak_measured"] = pk["mfma_i8_tops"]
+            res["roofline"]["frac_measured"] = round(gemm_tops / pk["mfma_i8_tops"], 4)
         res["selector_frac_measured_read_peak"] = round(main_cfg["selector_gbs"] / pk["hbm_read_gbs"], 4)
     hot_ms = gemm_hot(cfg, st)
     res["gemm_hot_cache"] = {"ms": round(hot_ms, 4),
