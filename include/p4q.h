@@ -377,11 +377,11 @@ int p4q_calib_block_grad(p4q_dtype dt, int M, int d, int f, int H, const void *x
  *     round across work-groups, which meet in the workspace (exact int32
  *     partial sums; the last to arrive writes the tile), or, below 128 x 128
  *     tiles, sums the slices in a second kernel;
- *   - for large products (M >= 1536, K_in >= 2048 and enough output tiles to
- *     fill the device): given that much, the call first rewrites both operands' codes
- *     there as 6-bit floats (3/4 byte per code, rows padded to 256) and
- *     contracts them on the 6-bit matrix instructions, whose fp32 sums of
- *     these integers are exact.
+ *   - for large products (M >= 1536, K_in >= 512 and enough output tiles to
+ *     fill the device, more of them below K_in = 4096): given that much, the
+ *     call first rewrites both operands' codes there as 6-bit floats (3/4 byte
+ *     per code, rows padded to 256) and contracts them on the 6-bit matrix
+ *     instructions, whose fp32 sums of these integers are exact.
  *   With ws NULL, smaller or misaligned the call runs without it.  The
  *   results are identical either way (integer sums).  The first 4096 bytes
  *   hold per-tile arrival counters, which calls with M < 1024 read and no

@@ -1332,24 +1332,26 @@ static bool use_mid_tiles(int M, int N) { return M > 16 && M < 1024 && N >= 1024
 // 4096 rows of K = 4096, 22 us at 11264 + 12288) and its 256 x 256 tiles take
 // one CU each, whose epilogue nothing covers, so it needs rows to spread the
 // pass over, tiles for more than half of the CUs, and k to cover the rest.
-// Measured, int8 / 6-bit us:
-//  * K = 4096, M x N = 11264 x 22016: 736 / 532, 4096 x 12288: 146 / 121, 1536 x
-//    12288: 80 / 78, 4096 x 4096 (256 tiles): 50 / 47; 1024 x 22016: 82 / 86,
-//    3072 x 4096 (192 tiles): 43 / 45, 2048 x 4096 (128 tiles): 35 / 42.  K =
-//    11008, 2304 x 4096 (144 tiles): 98 / 82, but 2048 x 4096 (128) 83 / 82.
-//  * Below K = 4096 only many tiles pay.  K = 3072: 512 tiles 82 / 74, 516: 101 /
-//    99; 384: 67 / 67, 288: 64 / 64, 280: 64 / 66, 256: 42 / 44.  K = 2048: 688
-//    tiles 84 / 80, 704: 84 / 80, 768: 86 / 80; 516: 73 / 76, 512: 61 / 61, 384: 47 /
-//    52, 256: 32 / 36.  K = 1024: 2112 tiles 138 / 140, 768: 53 / 59, 256: 22 / 28.
-//    K = 512: 3784 tiles 157 / 167, 256: 15 / 21; K = 128, 2112: 56 / 81, 228: 14 / 26.
+// Measured, int8 / 6-bit us (random codes, rewrite included):
+//  * K = 4096, M x N = 11264 x 22016: 733 / 545, 4096 x 12288: 149 / 120, 1536 x
+//    12288: 80 / 76, 4096 x 4096 (256 tiles): 51 / 47, 1792 x 8192 (224): 46.7 / 45.1;
+//    1280 x 22016: 90 / 87, 1024 x 22016: 81 / 84, 3072 x 4096 (192 tiles): 43.3 /
+//    43.2, 2048 x 4096 (128): 35 / 40.
+//  * Longer rows pay from fewer tiles: K = 5120, 1536 x 5632 (132): 49 / 45; K =
+//    11008, 2304 x 4096 (144): 97 / 80, 2048 x 4096 (128): 81 / 79.
+//  * Shorter ones need many, tiles x K^2 >= 5 x 2^29.  On that line: K = 3072, 287
+//    tiles: 62 / 60; 2560, 410: 61 / 58; 2048, 640: 75 / 72; 1536, 1152: 100 / 97; 1024,
+//    2596: 333 / 333; 512, 10340: 443 / 401.  Above it: K = 3072, 512: 78 / 75; 2048,
+//    768: 85 / 78; 1024, 3784: 236 / 206.  Below: K = 2048, 516: 73.1 / 73.5, 384: 47 /
+//    51; 1024, 768: 52 / 58, 256: 21 / 26; 512, 3784: 159 / 160, 256: 16 / 21; 256, 27730:
+//    852 / 856; 128, 2112: 56 / 76.
 // The operands' copy is kept under 1 GiB.
 constexpr int kF6MinRows = 1536;
-constexpr int kF6MinK = 2048;
 static bool use_f6(int M, int N, int K) {
-    if (!use_large_tiles(M, N) || M < kF6MinRows || K < kF6MinK) return false;
+    if (!use_large_tiles(M, N) || M < kF6MinRows || K < 512) return false;
     const int64_t T = (((int64_t)M + 255) / 256) * (((int64_t)N + 255) / 256);
-    const int64_t least = K >= 5120 ? 129 : K >= 4096 ? 224 : (5 << 18) / K;   // 640 at K = 2048, 426 at 3072
-    return T >= least && T < (1 << 30) && gemm_f6_bytes(M, N, K) <= ((size_t)1 << 30);
+    const bool pays = K >= 5120 ? T > 128 : K >= 4096 ? T >= 224 : T * K * K >= (int64_t)5 << 29;
+    return pays && T < (1 << 30) && gemm_f6_bytes(M, N, K) <= ((size_t)1 << 30);
 }
 
 // Tile height of the mid path: 128 rows, or 64 where 128-row tiles would

@@ -357,8 +357,8 @@ def test_linear_workspace_size_extremes(args):
 
 @pytest.mark.parametrize("shape,six_bit", [
     ((11264, 12288, 4096), True), ((4096, 4096, 4096), True), ((2304, 4096, 11008), True),
-    ((4096, 12288, 2048), True), ((2048, 12288, 3584), True),
-    ((11264, 22016, 1024), False), ((11264, 22016, 128), False), ((4096, 4096, 3072), False),
+    ((4096, 12288, 2048), True), ((2048, 12288, 3584), True), ((11264, 22016, 1024), True),
+    ((11264, 12288, 1024), False), ((11264, 22016, 128), False), ((4096, 4096, 3072), False),
     ((2048, 12288, 2048), False), ((1535, 22016, 4096), False), ((2048, 4096, 11008), False)])
 def test_linear_workspace_only_where_the_6bit_path_pays(shape, six_bit):
     """Large products ask for the room of the 6-bit path, those of short rows

@@ -416,7 +416,7 @@ def test_several_tiles_per_work_group(shape):
     ap, sa, wp, sw = codes_for(M, N, K, seed=M + N + K)
     ops = [to_gpu(t) for t in (ap, sa, wp, sw)]
     ws = p4q.w4a4_linear_workspace(M, N, K, dev)
-    assert (ws is not None) == (K >= 2048)
+    assert (ws is not None) == (K == 4096)
     none = torch.empty(0, dtype=torch.uint8, device=dev)
     rng = np.random.default_rng(K)
     for dt in (torch.bfloat16, torch.float16):
