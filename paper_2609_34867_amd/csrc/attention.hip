@@ -28,10 +28,10 @@
 //    latency 32 times per tile.
 //  * Work-groups of one (sample, head) are neighbours on one XCD, longest
 //    first, so K and V come from its L2 after the first of them.
-// At 16 x 704 tokens and 32 heads: 128 us, against 172 us for the form that
-// staged K and V^T through registers, read operands as needed and masked
-// through a branch per score; one sample of 371 tokens, 40 heads: 12.6
-// against 16.5 us.  Per SIMD its vector instructions take 39 us, its MFMAs 28
+// At 16 x 704 tokens and 32 heads a call takes 123 us (the kernel 121),
+// against 166 us for the form that staged K and V^T through registers, read
+// operands as needed and masked through a branch per score; one sample of 371
+// tokens, 40 heads: 13.0 (12.6) against 16.6 us.  Per SIMD its vector instructions take 39 us, its MFMAs 28
 // us; q, k, v and the output take 73 us at the rate of a copy.  Reading Q
 // and writing the output of 128 queries alone (no tiles) takes 42 us, each
 // tile of the two work-groups on a CU 2 us, most of it waiting: two

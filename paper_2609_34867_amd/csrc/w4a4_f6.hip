@@ -147,11 +147,12 @@ __device__ __forceinline__ void hold_acc(v4f (&acc)[NF][NF]) {
 //    one, stage g + 1 is read into the other.  So stage g's slot is free as
 //    soon as stage g starts, and the DMA of stage g + 3 goes into it: two
 //    whole stages are always in flight.
-//  * Measured, M x N x K = 11264 x 12288 x 4096, random codes: 296 us, against
-//    425 us of the int8 kernel; 216 us is what its MFMAs alone take on nine
-//    rounds of tiles (8.25 full), at the clock the power limit leaves them
-//    (28 cycles of 2.4 GHz per MFMA instead of 18); its data movement alone
-//    takes 204 us.
+//  * Measured, M x N x K = 11264 x 12288 x 4096: 277 us in the batch-16 step,
+//    against 387 us of the int8 kernel there; the four products of a 7B layer
+//    at 11264 rows 1092 us (1139 with four registers spilled, before hold_acc).
+//    With random codes, 216 us is what its MFMAs alone take on nine rounds of
+//    tiles (8.25 full), at the clock the power limit leaves them (28 cycles of
+//    2.4 GHz per MFMA instead of 18); its data movement alone takes 204 us.
 //  * KT, the number of stages, is even (the operands are padded with a stage
 //    of zeros), so a tile starts and ends on the same set.
 template <bool BF16OUT, bool ACC>
